@@ -335,6 +335,10 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
  * with two_sweeps set (the default), FP32 sweeps run two sweeps per launch on blocks of 1024
  * lanes marching z_chunk2 cells: rows of 64 lanes (16 rows) or, where that wastes fewer lanes
  * on the box, rows of 32 lanes (32 rows), two cells per lane for even nx and one for odd.
+ * FP32 correction sweeps of a box that fits the chip's registers (about 4 million cells) run a
+ * whole chunk per launch instead, one workgroup per CU exchanging sub-box faces with its
+ * neighbours (the same arithmetic cell by cell); a context whose shapes were set by
+ * socfv_set_tiles runs the launches asked for.
  * socfv_set_tiles overrides them for a context (0 = keep; two_sweeps: -1 keep, 0 off, 1 on
  * with the row width chosen for the box, 2 on with 64-lane rows, 3 on with 32-lane rows; a
  * new row width re-picks z_chunk2 unless given); socfv_autotune times candidate shapes on
@@ -343,6 +347,14 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
  */
 int socfv_set_tiles(socfv_ctx *c, int tile_y, int z_chunk, int z_chunk2, int two_sweeps);
 int socfv_autotune(socfv_ctx *c, int sweeps, int best[3], void *hip_stream);
+
+/*
+ * Longest time (s, default 1) that a workgroup of a resident launch waits for its neighbours.
+ * They run together on an otherwise idle GPU; where other work holds CUs for longer, the launch
+ * is given up, its input is intact, and the solve goes on with two-sweep launches (from then on
+ * for this context).  0 gives up at the first value that is not there yet.
+ */
+int socfv_set_wait_limit(socfv_ctx *c, double seconds);
 
 /* Problem facts: dims[3] = nx, ny, nz; counts[3] = pore cells, reactive cells,
  * cells not connected (always 0 after a successful setup). */

@@ -12,7 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsocfv.so")
-SOURCES = ["kernels.hip", "flow.hip", "api.cpp"]
+SOURCES = ["kernels.hip", "resident.hip", "flow.hip", "api.cpp"]
 
 # Packed FP32 instructions are disabled for every HIP compile of this library.
 HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -89,6 +89,13 @@ struct socfv_ctx {
   int md_pinned = -1;
   Tiles tiles{4, 8, 32, 1};
   bool tiles_fixed = false;
+  // resident sweeps: the box's split (C = 0: none), its exchange words and the next tag
+  ResidentPlan res{};
+  bool res_planned = false;
+  unsigned long long *inbox = nullptr;
+  void *res_diag = nullptr;
+  unsigned tag = 1;
+  unsigned long long wait_limit = 100000000ull;   // ticks of the 100 MHz clock: 1 s
   int ncu = 1;                   // compute units of the device (for the tile choice)
   int dev = 0;                   // device holding the context's buffers
   // last forward solution
@@ -206,6 +213,32 @@ int ensure_state(socfv_ctx *c) {
   for (hipEvent_t &e : c->evp)
     if (!e) HIPCHK(hipEventCreate(&e));
   return ensure_partial(c, partial_need(c->g, c->tiles));
+}
+
+// The resident split of this problem with its exchange buffer, if the box fits the chip and
+// no launch shape was asked for.
+int ensure_resident(socfv_ctx *c) {
+  if (!c->res_planned) {
+    c->res_planned = true;
+    if (two_path(c->g)) c->res = resident_plan(c->g, 4, c->ncu);
+  }
+  if (!c->res.C || c->inbox) return 0;
+  const long long words = 2 * c->res.slot_words;
+  const long long diag = resident_diag_bytes(c->res, 4);
+  if (hipMalloc(&c->inbox, sizeof(unsigned long long) * (size_t)words) != hipSuccess ||
+      (diag && hipMalloc(&c->res_diag, (size_t)diag) != hipSuccess)) {
+    (void)hipGetLastError();
+    hfree(c->inbox);
+    c->inbox = nullptr;
+    c->res_diag = nullptr;
+    c->res.C = 0;                        // no room: the two-sweep launches need none
+    return 0;
+  }
+  // words of an earlier buffer at this address could carry a tag of this one
+  launch_fill_f64((double *)c->inbox, words, 0.0, c->st);
+  HIPCHK(hipGetLastError());
+  c->tag = 1;
+  return ensure_partial(c, (long long)NV * c->res.gx * c->res.gy * c->res.gz + 64);
 }
 
 int ensure_adjoint(socfv_ctx *c) {
@@ -346,6 +379,37 @@ struct Solver {
     return nb;
   }
 
+  bool resident() const { return c->res.C > 0 && c->inbox && !c->tiles_fixed; }
+
+  // Enqueue k correction sweeps buf[cur] -> buf[cur ^ 1] as one resident launch (gate, fill:
+  // device flags, nullable); returns the partials' block count.
+  int launch_resident_sweeps(int &cur, int k, bool adj, double gscale, const int *gate,
+                             const int *fill) {
+    const ResidentPlan &rp = c->res;
+    const int nb = rp.gx * rp.gy * rp.gz;
+    if (c->tag > 0xffffffffu - (unsigned)k) {
+      launch_fill_f64((double *)c->inbox, 2 * rp.slot_words, 0.0, c->st);
+      c->tag = 1;
+    }
+    SweepArgs<float> a = sweep_args<float>(c->s32[cur], c->s32[cur ^ 1], true, c->partial);
+    a.w = faces32(c);
+    a.gscale = (float)gscale;
+    a.gate = gate;
+    ResidentArgs r{};
+    r.K = k;
+    r.tag0 = c->tag;
+    r.inbox = c->inbox;
+    r.diag = c->res_diag;
+    r.abort = &c->dctl->lost;
+    r.limit = c->wait_limit;
+    r.fill = fill;
+    r.adj = adj;
+    launch_resident(a, rp, r, c->st);
+    c->tag += (unsigned)k;
+    cur ^= 1;
+    return nb;
+  }
+
   // k sweeps (as launch_sweeps), timed, then their partials reduced on the host
   template <typename T>
   int chunk(T *buf0, T *buf1, int &cur, int k, bool dc, Faces<T> w, double out[NV]) {
@@ -424,8 +488,9 @@ struct Solver {
   }
 
   // FP32 correction cycles with the loop's decisions on the device (SolveCtl): per chunk
-  // of K sweeps, the corrections are zeroed if a cycle starts (k_fill2_gated), the sweeps run
-  // while the state is CTL_RUN, k_ctl_chunk takes the correction residual and the cycle's end
+  // of K sweeps, the corrections are zeroed if a cycle starts (k_fill2_gated, or by the resident
+  // launch itself), the sweeps run while the state is CTL_RUN (one resident launch where the box
+  // fits the chip, else K / 2 two-sweep launches), k_ctl_chunk takes the correction residual and the cycle's end
   // test, the refresh runs if it asked for one, and k_ctl_refresh applies the stop rule and
   // starts the next cycle.  The host enqueues groups of chunks and reads the state once per
   // group; launches after the stop return at once.  From s64[cur] with FP64 residual res.
@@ -448,23 +513,32 @@ struct Solver {
     h.res = res;
     h.ri = INFINITY;
     const long long budget = h.max_iter;
+    TRY(ensure_resident(c));
     HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
     const int nbr = march64_blocks(c->g);
     long long known = 0;                 // sweeps done at the last read of the state
     long long it_prev = -1;              // sweeps and correction residual at the read before
     double ri_prev = 0;
     int ng = 2;                          // chunks in the next group
+    int cd = 0;                          // buffer holding the correction
+    bool whole = resident();             // a chunk is one resident launch
     for (;;) {
-      int ks[G];
+      int ks[G], from[G];
       int nch = 0;
       long long enq = known;
       for (; nch < ng && enq < budget; ++nch) {
         const int k = (int)std::min<long long>(K, budget - enq);
-        launch_fill_gated(c->s32[0], c->s32[1], n, c->dctl, c->st);
-        HIPCHK(hipEventRecord(c->evp[4 * nch], c->st));
-        int cd = 0;
-        const long long nb = launch_sweeps<float>(c->s32[0], c->s32[1], cd, k, true, faces32(c),
-                                                  &c->dctl->state);
+        from[nch] = cd;
+        long long nb;
+        if (whole) {
+          HIPCHK(hipEventRecord(c->evp[4 * nch], c->st));
+          nb = launch_resident_sweeps(cd, k, false, 0.0, &c->dctl->state, &c->dctl->fill);
+        } else {
+          launch_fill_gated(c->s32[0], c->s32[1], n, c->dctl, c->st);
+          HIPCHK(hipEventRecord(c->evp[4 * nch], c->st));
+          nb = launch_sweeps<float>(c->s32[0], c->s32[1], cd, k, true, faces32(c),
+                                    &c->dctl->state);
+        }
         HIPCHK(hipEventRecord(c->evp[4 * nch + 1], c->st));
         launch_ctl_chunk(c->dctl, c->partial, (int)nb, k, c->st);
         RefreshArgs a;
@@ -498,6 +572,21 @@ struct Solver {
       }
       std::sort(refresh_ms, refresh_ms + nch);
       for (int g = nch - 1; g >= 0 && g >= nch - (h.cycles - cyc0); --g) msref += refresh_ms[g];
+      if (h.state == CTL_LOST) {
+        // the chunk after the last one that ran was given up: its input is as it was, and the
+        // two-sweep launches go on from there
+        long long it = known;
+        int g = 0;
+        while (it < h.it) it += ks[g++];
+        cd = from[g];
+        whole = false;
+        c->res.C = 0;
+        h.state = CTL_RUN;
+        h.lost = 0;
+        known = h.it;
+        HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
+        continue;
+      }
       known = h.it;
       if (h.state == CTL_DIVERGED || h.state == CTL_DONE || h.state == CTL_STOP || nch == 0) break;
       // next group: about half the chunks the residual's decay rate since the last read
@@ -651,6 +740,8 @@ void socfv_destroy(socfv_ctx *c) {
   hfree(c->aux64);
   hfree(c->aux64b);
   hfree(c->partial);
+  hfree(c->inbox);
+  hfree(c->res_diag);
   hfree(c->dres);
   if (c->hres) (void)hipHostFree(c->hres);
   hfree(c->dctl);
@@ -960,6 +1051,17 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
     long long nb = S.nblk;
     int j = 0;
     if constexpr (std::is_same_v<T, float>) {
+      if (dc && S.resident()) {
+        const int from = cc;
+        nb = S.launch_resident_sweeps(cc, k, true, gs, nullptr, nullptr);
+        HIPCHK(hipMemcpyAsync(&c->hctl->lost, &c->dctl->lost, sizeof(int), hipMemcpyDeviceToHost,
+                              c->st));
+        HIPCHK(hipGetLastError());
+        TRY(reduce_to_host(c, (int)nb, NV, 0u, out));
+        if (!c->hctl->lost) return 0;
+        cc = from;                       // given up: its input is as it was
+        c->res.C = 0;
+      }
       // FP32 corrections: two transpose sweeps per launch where the shape allows; an odd
       // remainder ends with one single sweep
       if (dc && two_path(c->g) && S.t.two) {
@@ -1000,6 +1102,9 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
     }
   } else {
     rel = 1.0;
+    TRY(ensure_resident(c));
+    *c->hctl = SolveCtl{};
+    HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
     while (rel >= p->tol && S.it < p->max_iter) {
       launch_fill_f32(c->s32[0], n, 0.0f, c->st);
       launch_fill_f32(c->s32[1], n, 0.0f, c->st);
@@ -1214,6 +1319,14 @@ int socfv_set_tiles(socfv_ctx *c, int tile_y, int z_chunk, int z_chunk2, int two
   return ensure_partial(c, partial_need(c->g, c->tiles));
 }
 
+int socfv_set_wait_limit(socfv_ctx *c, double seconds) {
+  if (!c) return fail(SOCFV_INVALID_ARG, "NULL context");
+  if (!(seconds >= 0.0) || seconds > 3600.0)
+    return fail(SOCFV_INVALID_ARG, "the wait limit must be in [0, 3600] s");
+  c->wait_limit = (unsigned long long)(seconds * 1e8);
+  return SOCFV_OK;
+}
+
 int socfv_autotune(socfv_ctx *c, int sweeps, int best[3], void *hip_stream) {
   if (!c) return fail(SOCFV_INVALID_ARG, "NULL context");
   if (!c->have_velocity) return fail(SOCFV_INVALID_ARG, "velocity not set");
@@ -1298,7 +1411,6 @@ int socfv_autotune(socfv_ctx *c, int sweeps, int best[3], void *hip_stream) {
   best_t.zc2 = best_zc2;
   best_t.two = c->tiles.two;
   c->tiles = best_t;
-  c->tiles_fixed = true;
   TRY(ensure_partial(c, partial_need(c->g, c->tiles)));
   TRY(leave(c, hip_stream));
   if (best) { best[0] = best_t.ty; best[1] = best_t.zc; best[2] = best_t.zc2; }

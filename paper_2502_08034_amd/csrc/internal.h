@@ -298,7 +298,8 @@ void launch_reduce(const double *partial, int nblk, int nv, unsigned maxmask, do
 // every chunk of sweeps are taken on the device, so the host enqueues many chunks between two
 // reads of the state.  Sweeps run while state == CTL_RUN; the refresh while CTL_REFRESH; the
 // corrections are zeroed before a chunk while `fill` is set.
-enum { CTL_RUN = 0, CTL_REFRESH = 1, CTL_DONE = 2, CTL_STOP = 3, CTL_DIVERGED = 4 };
+enum { CTL_RUN = 0, CTL_REFRESH = 1, CTL_DONE = 2, CTL_STOP = 3, CTL_DIVERGED = 4,
+       CTL_LOST = 5 };      // a resident launch was given up: its chunk has not run
 struct SolveCtl {
   int state;            // CTL_*
   int fill;             // zero the corrections before the next chunk
@@ -307,7 +308,7 @@ struct SolveCtl {
   long long it;         // FP32 sweeps done
   long long max_iter;
   int cycles;           // refreshes after the first
-  int pad;
+  int lost;             // raised by a resident launch that ran into its time limit
   double tol, tau, npore, reduction;   // stop tolerance, time scale, pore cells, per-cycle drop
   double target, best, res, ri;        // cycle target, best correction residual, last FP64 /
                                        // correction residual
@@ -330,6 +331,39 @@ void launch_refresh_gated(const RefreshArgs &a, double *s64_0, double *s64_1,
                           const SolveCtl *ctl, hipStream_t st);
 // zero two FP32 buffers of n values when ctl->fill is set
 void launch_fill_gated(float *a, float *b, long long n, const SolveCtl *ctl, hipStream_t st);
+
+// Resident sweeps: K sweeps of the correction in one launch, the box split into sub-boxes of
+// X x Y columns of C cells, one sub-box per workgroup (resident.hip).
+constexpr int RESIDENT_LANES = 512;            // lanes (columns) per workgroup
+constexpr int RESIDENT_LDS = 156 * 1024;       // most LDS a sub-box may take
+constexpr int RESIDENT_LDS_ALONE = 84 * 1024;  // more than half a CU's: one workgroup per CU
+struct ResidentPlan {
+  int C;                // cells per lane along z; 0: the box does not fit
+  int X, Y;             // columns of a sub-box
+  int gx, gy, gz;       // sub-boxes along x, y, z
+  int lds;              // bytes of LDS per workgroup
+  long long block_words, slot_words;   // exchange words per workgroup, and per slot
+};
+// bytes: of a value (4 or 8)
+ResidentPlan resident_plan(const Grid &g, int bytes, int ncu);
+// bytes of ResidentArgs::diag (0: not used by this plan)
+long long resident_diag_bytes(const ResidentPlan &pl, int bytes);
+struct ResidentArgs {
+  int X, Y, gx, gy, gz;
+  int K;                // sweeps of the launch
+  unsigned tag0;        // tag of the first sweep; K - 1 tags are used
+  unsigned long long *inbox;     // exchange words: two slots, each a run per workgroup
+  long long block_words, slot_words;
+  void *diag;           // lean columns: the diagonals
+  int *abort;           // raised when a wait ran into its limit; the launch's output is void
+  unsigned long long limit;      // longest wait, in ticks of the 100 MHz wall clock
+  const int *fill;      // nullable: nonzero = start from zero instead of a.s
+  int adj;              // sweeps of the transpose system
+};
+// a.partial is written (one entry per workgroup); a.s and a.s_new must differ
+template <typename T>
+void launch_resident(const SweepArgs<T> &a, const ResidentPlan &pl, const ResidentArgs &args,
+                     hipStream_t st);
 
 // Static scratch of the allocation-free entry point: SCRATCH_DOUBLES doubles of device memory
 // per GPU.  scratch_address gives its device address on device dev (which must be current at

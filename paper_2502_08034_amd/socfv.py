@@ -93,6 +93,7 @@ def _load():
         "socfv_solve_stokes": (i, [P, C.POINTER(FlowParams), P, P, P, P,
                                    C.POINTER(FlowStats), P]),
         "socfv_set_tiles": (i, [P, i, i, i, i]),
+        "socfv_set_wait_limit": (i, [P, d]),
         "socfv_autotune": (i, [P, i, C.POINTER(C.c_int), P]),
         "socfv_info": (i, [P, C.POINTER(C.c_int), C.POINTER(C.c_long)]),
         "socfv_destroy": (None, [P]),
@@ -348,6 +349,10 @@ def solve_soc_upsampled(ctx: Context, p: Params, want_state=True):
 def set_tiles(ctx: Context, tile_y=0, z_chunk=0, z_chunk2=0, two_sweeps=-1):
     _check(_lib.socfv_set_tiles(ctx.handle, int(tile_y), int(z_chunk), int(z_chunk2),
                                 int(two_sweeps)))
+
+
+def set_wait_limit(ctx: Context, seconds=1.0):
+    _check(_lib.socfv_set_wait_limit(ctx.handle, float(seconds)))
 
 
 def autotune(ctx: Context, sweeps=20):

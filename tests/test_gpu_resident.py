@@ -1,0 +1,108 @@
+"""Resident sweeps (a chunk of sweeps in one launch) against the two-sweep launches and the
+oracle (needs an MI355X).
+
+Both forms compute a cell's update with the same operations in the same order, so their states
+are equal bit for bit after an even number of sweeps (an odd remainder of the two-sweep launches
+is a single sweep of other arithmetic); the oracle bound is that of the other FP32 forms (1e-5 after 401 updates,
+see test_gpu_fp32_parity).  Boxes cover every column length, one workgroup and many, ragged
+sub-boxes in x, y and z, a top plane of one cell, and chunks of two to 401 sweeps.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_08034_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+FINITE = dict(s_in=1.0, s_eq=0.0, Da=0.45, mode=0)
+PINNED = dict(s_in=0.0, s_eq=1.0, Da=0.0, mode=1)
+
+
+@pytest.fixture(scope="module")
+def sv():
+    from paper_2502_08034_amd import socfv
+    assert torch.cuda.is_available()
+    return socfv
+
+
+def inputs_of(shape, kappa=False):
+    nx, ny, nz = shape
+    if min(ny, nz) < 12:                         # plain channel
+        solid, u = I.plug_flow_case(nx, ny, nz, 0.7)
+    else:
+        solid = I.fibres_nonoverlap(nx, ny, nz, 2.5, 0.88, 7).solid
+        u = I.darcy_velocity(solid, 1.0, device="cuda", as_numpy=False)
+    return solid, u, I.lognormal_activity(solid, 0.3, seed=9) if kappa else None
+
+
+def problem(sv, inputs):
+    solid, u, k = inputs
+    return sv.Problem.create(solid, *u, kappa=k)
+
+
+def both(sv, pb, **kw):
+    """The resident launches' state and the two-sweep launches' (and their statistics)."""
+    p = sv.params(precision="fp32", **kw)
+    out = [sv.solve_soc_steady(pb.ctx, p)]
+    if kw["mode"] == 0:
+        out.append(sv.solve_soc_adjoint(pb.ctx, p, want_psi=True)[2:])
+    sv.set_tiles(pb.ctx, 0, 0, 0, 1)
+    out.append(sv.solve_soc_steady(pb.ctx, p))
+    if kw["mode"] == 0:
+        out.append(sv.solve_soc_adjoint(pb.ctx, p, want_psi=True)[2:])
+    return out
+
+
+@pytest.mark.parametrize("shape,kappa,mode", [
+    ((1, 1, 1), False, FINITE), ((33, 3, 2), False, FINITE), ((600, 3, 2), True, FINITE),
+    ((5, 600, 7), False, FINITE), ((7, 5, 901), False, FINITE),         # few columns, long ones
+    ((64, 32, 33), False, PINNED), ((131, 33, 41), True, FINITE),       # 4 cells a column
+    ((129, 63, 65), False, FINITE),                                     # 8
+    ((175, 89, 89), False, PINNED),                                     # 12
+    ((191, 97, 95), True, FINITE),                                      # 16
+    ((253, 97, 99), False, FINITE),                                     # 20
+    ((256, 120, 118), False, PINNED), ((256, 128, 128), False, FINITE),  # lean columns
+    ((256, 128, 127), False, PINNED),
+])
+def test_resident_sweeps_equal_the_two_sweep_launches(sv, shape, kappa, mode):
+    inputs = inputs_of(shape, kappa)
+    for check, sweeps in ((200, 400), (2, 6), (30, 70)):
+        runs = both(sv, problem(sv, inputs), tol=0.0, max_iter=sweeps, check_every=check, **mode)
+        half = len(runs) // 2
+        for a, b in zip(runs[:half], runs[half:]):
+            assert a[1].iterations == b[1].iterations == sweeps
+            assert torch.equal(a[0], b[0]), (shape, check, sweeps)
+
+
+@pytest.mark.parametrize("mode", [FINITE, PINNED])
+def test_resident_sweeps_match_the_oracle(sv, orc, mode):
+    inputs = inputs_of((67, 35, 29))
+    pb, solid, u = problem(sv, inputs), inputs[0], inputs[1]
+    u = [np.asarray(v.cpu() if isinstance(v, torch.Tensor) else v) for v in u]
+    op = orc.Problem(solid, *u, s_in=mode["s_in"], s_eq=mode["s_eq"], Da=mode["Da"],
+                     pinned=bool(mode["mode"]))
+    s0 = op.initial_state()
+    r0, _ = orc.residual(op, s0)
+    ref = s0 + orc.correction_iterate(op, r0, 0.4 / orc.max_diag(op), 401)
+    s, st = sv.solve_soc_steady(pb.ctx, sv.params(precision="fp32", tol=0.0, max_iter=401,
+                                                  check_every=401, **mode))
+    assert st.iterations == 401
+    assert np.abs(s.cpu().numpy() - ref)[solid == 0].max() <= 1e-5
+
+
+def test_a_launch_that_is_given_up_loses_nothing(sv):
+    # wait limit 0: every resident launch is given up at its first missing value, and the solve
+    # and the adjoint go on with the two-sweep launches from the untouched input
+    inputs = inputs_of((96, 48, 40))
+    ref, pb = problem(sv, inputs), problem(sv, inputs)
+    sv.set_wait_limit(pb.ctx, 0.0)
+    with pytest.raises(sv.SocfvError):
+        sv.set_wait_limit(pb.ctx, -1.0)
+    p = sv.params(precision="fp32", tol=1e-8, check_every=100, **FINITE)
+    for _ in range(2):
+        (s, st), (r, rt) = sv.solve_soc_steady(pb.ctx, p), sv.solve_soc_steady(ref.ctx, p)
+        assert st.status == sv.OK and st.iterations == rt.iterations
+        assert torch.equal(s, r)
+        ga, gb = sv.solve_soc_adjoint(pb.ctx, p), sv.solve_soc_adjoint(ref.ctx, p)
+        assert torch.equal(ga[0], gb[0]) and ga[3].iterations == gb[3].iterations
