@@ -89,11 +89,13 @@ struct socfv_ctx {
   int md_pinned = -1;
   Tiles tiles{4, 8, 32, 1};
   bool tiles_fixed = false;
-  // resident sweeps: the box's split (C = 0: none), its exchange words and the next tag
-  ResidentPlan res{};
+  // resident sweeps: the box's FP32 and FP64 splits (C = 0: none), their exchange words and the
+  // next tag
+  ResidentPlan res{}, res64{};
   bool res_planned = false;
   unsigned long long *inbox = nullptr;
   void *res_diag = nullptr;
+  long long inbox_words = 0;
   unsigned tag = 1;
   unsigned long long wait_limit = 100000000ull;   // ticks of the 100 MHz clock: 1 s
   int ncu = 1;                   // compute units of the device (for the tile choice)
@@ -215,30 +217,38 @@ int ensure_state(socfv_ctx *c) {
   return ensure_partial(c, partial_need(c->g, c->tiles));
 }
 
-// The resident split of this problem with its exchange buffer, if the box fits the chip and
-// no launch shape was asked for.
+// The resident splits of this problem with their exchange buffer, if the box fits the chip.
 int ensure_resident(socfv_ctx *c) {
   if (!c->res_planned) {
     c->res_planned = true;
-    if (two_path(c->g)) c->res = resident_plan(c->g, 4, c->ncu);
+    if (two_path(c->g)) {
+      c->res = resident_plan(c->g, 4, c->ncu);
+      c->res64 = resident_plan(c->g, 8, c->ncu);
+    }
   }
-  if (!c->res.C || c->inbox) return 0;
-  const long long words = 2 * c->res.slot_words;
-  const long long diag = resident_diag_bytes(c->res, 4);
-  if (hipMalloc(&c->inbox, sizeof(unsigned long long) * (size_t)words) != hipSuccess ||
+  if ((!c->res.C && !c->res64.C) || c->inbox) return 0;
+  long long diag = 0, blocks = 0;
+  c->inbox_words = 0;
+  for (const ResidentPlan *p : {&c->res, &c->res64}) {
+    if (!p->C) continue;
+    c->inbox_words = std::max(c->inbox_words, 2 * p->slot_words);
+    diag = std::max(diag, resident_diag_bytes(*p, p == &c->res ? 4 : 8));
+    blocks = std::max(blocks, (long long)p->gx * p->gy * p->gz);
+  }
+  if (hipMalloc(&c->inbox, sizeof(unsigned long long) * (size_t)c->inbox_words) != hipSuccess ||
       (diag && hipMalloc(&c->res_diag, (size_t)diag) != hipSuccess)) {
     (void)hipGetLastError();
     hfree(c->inbox);
     c->inbox = nullptr;
     c->res_diag = nullptr;
-    c->res.C = 0;                        // no room: the two-sweep launches need none
+    c->res.C = c->res64.C = 0;           // no room: the other launches need none
     return 0;
   }
   // words of an earlier buffer at this address could carry a tag of this one
-  launch_fill_f64((double *)c->inbox, words, 0.0, c->st);
+  launch_fill_f64((double *)c->inbox, c->inbox_words, 0.0, c->st);
   HIPCHK(hipGetLastError());
   c->tag = 1;
-  return ensure_partial(c, (long long)NV * c->res.gx * c->res.gy * c->res.gz + 64);
+  return ensure_partial(c, NV * blocks + 64);
 }
 
 int ensure_adjoint(socfv_ctx *c) {
@@ -379,22 +389,24 @@ struct Solver {
     return nb;
   }
 
-  bool resident() const { return c->res.C > 0 && c->inbox && !c->tiles_fixed; }
+  template <typename T>
+  ResidentPlan &res_plan() const {
+    return sizeof(T) == 4 ? c->res : c->res64;
+  }
+  template <typename T>
+  bool resident() const {
+    return res_plan<T>().C > 0 && c->inbox && !c->tiles_fixed;
+  }
 
-  // Enqueue k correction sweeps buf[cur] -> buf[cur ^ 1] as one resident launch (gate, fill:
-  // device flags, nullable); returns the partials' block count.
-  int launch_resident_sweeps(int &cur, int k, bool adj, double gscale, const int *gate,
-                             const int *fill) {
-    const ResidentPlan &rp = c->res;
-    const int nb = rp.gx * rp.gy * rp.gz;
+  // Enqueue k sweeps a.s -> a.s_new as one resident launch (fill: device flag, nullable);
+  // returns the partials' block count.
+  template <typename T>
+  long long launch_resident_sweeps(const SweepArgs<T> &a, int k, bool adj, const int *fill) {
+    const ResidentPlan &rp = res_plan<T>();
     if (c->tag > 0xffffffffu - (unsigned)k) {
-      launch_fill_f64((double *)c->inbox, 2 * rp.slot_words, 0.0, c->st);
+      launch_fill_f64((double *)c->inbox, c->inbox_words, 0.0, c->st);
       c->tag = 1;
     }
-    SweepArgs<float> a = sweep_args<float>(c->s32[cur], c->s32[cur ^ 1], true, c->partial);
-    a.w = faces32(c);
-    a.gscale = (float)gscale;
-    a.gate = gate;
     ResidentArgs r{};
     r.K = k;
     r.tag0 = c->tag;
@@ -404,20 +416,56 @@ struct Solver {
     r.limit = c->wait_limit;
     r.fill = fill;
     r.adj = adj;
-    launch_resident(a, rp, r, c->st);
+    launch_resident<T>(a, rp, r, c->st);
     c->tag += (unsigned)k;
-    cur ^= 1;
-    return nb;
+    return (long long)rp.gx * rp.gy * rp.gz;
+  }
+
+  // The same with the partials reduced on the host; false if the launch was given up (its input
+  // is as it was, and this context takes the other launches from then on).
+  template <typename T>
+  int resident_chunk(const SweepArgs<T> &a, int k, bool adj, double out[NV], bool &ran) {
+    const long long nb = launch_resident_sweeps<T>(a, k, adj, nullptr);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(&c->hctl->lost, &c->dctl->lost, sizeof(int), hipMemcpyDeviceToHost,
+                          c->st));
+    TRY(reduce_to_host(c, (int)nb, NV, 0u, out));
+    ran = !c->hctl->lost;
+    if (!ran) {
+      res_plan<T>().C = 0;
+      TRY(clear_ctl());
+    }
+    return 0;
+  }
+
+  int clear_ctl() {
+    *c->hctl = SolveCtl{};
+    HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
+    HIPCHK(hipStreamSynchronize(c->st));
+    return 0;
   }
 
   // k sweeps (as launch_sweeps), timed, then their partials reduced on the host
   template <typename T>
   int chunk(T *buf0, T *buf1, int &cur, int k, bool dc, Faces<T> w, double out[NV]) {
-    HIPCHK(hipEventRecord(c->t0, c->st));
-    const long long nb = launch_sweeps<T>(buf0, buf1, cur, k, dc, w, nullptr);
-    HIPCHK(hipEventRecord(c->t1, c->st));
-    HIPCHK(hipGetLastError());
-    TRY(reduce_to_host(c, (int)nb, NV, 0u, out));
+    bool ran = false;
+    if (sizeof(T) == 8 && resident<T>()) {
+      T *buf[2] = {buf0, buf1};
+      SweepArgs<T> a = sweep_args<T>(buf[cur], buf[cur ^ 1], dc, c->partial);
+      a.w = w;
+      HIPCHK(hipEventRecord(c->t0, c->st));
+      TRY(resident_chunk<T>(a, k, false, out, ran));
+      HIPCHK(hipEventRecord(c->t1, c->st));
+      HIPCHK(hipEventSynchronize(c->t1));
+      if (ran) cur ^= 1;
+    }
+    if (!ran) {
+      HIPCHK(hipEventRecord(c->t0, c->st));
+      const long long nb = launch_sweeps<T>(buf0, buf1, cur, k, dc, w, nullptr);
+      HIPCHK(hipEventRecord(c->t1, c->st));
+      HIPCHK(hipGetLastError());
+      TRY(reduce_to_host(c, (int)nb, NV, 0u, out));
+    }
     float ms = 0;
     HIPCHK(hipEventElapsedTime(&ms, c->t0, c->t1));
     (sizeof(T) == 4 ? ms32 : ms64) += ms;
@@ -513,7 +561,6 @@ struct Solver {
     h.res = res;
     h.ri = INFINITY;
     const long long budget = h.max_iter;
-    TRY(ensure_resident(c));
     HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
     const int nbr = march64_blocks(c->g);
     long long known = 0;                 // sweeps done at the last read of the state
@@ -521,7 +568,7 @@ struct Solver {
     double ri_prev = 0;
     int ng = 2;                          // chunks in the next group
     int cd = 0;                          // buffer holding the correction
-    bool whole = resident();             // a chunk is one resident launch
+    bool whole = resident<float>();             // a chunk is one resident launch
     for (;;) {
       int ks[G], from[G];
       int nch = 0;
@@ -532,7 +579,11 @@ struct Solver {
         long long nb;
         if (whole) {
           HIPCHK(hipEventRecord(c->evp[4 * nch], c->st));
-          nb = launch_resident_sweeps(cd, k, false, 0.0, &c->dctl->state, &c->dctl->fill);
+          SweepArgs<float> a = sweep_args<float>(c->s32[cd], c->s32[cd ^ 1], true, c->partial);
+          a.w = faces32(c);
+          a.gate = &c->dctl->state;
+          nb = launch_resident_sweeps<float>(a, k, false, &c->dctl->fill);
+          cd ^= 1;
         } else {
           launch_fill_gated(c->s32[0], c->s32[1], n, c->dctl, c->st);
           HIPCHK(hipEventRecord(c->evp[4 * nch], c->st));
@@ -616,6 +667,8 @@ struct Solver {
 
   int solve(const double *s_init, double *res_final, int *state_buf) {
     TRY(setup());
+    TRY(ensure_resident(c));
+    TRY(clear_ctl());
     const long long n = c->g.n;
     launch_init_state(c->g, c->flags, s_init, p->s_in, p->s_eq, pinned, c->s64[0], c->st);
     HIPCHK(hipGetLastError());
@@ -1017,6 +1070,8 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
   TRY(enter(c, hip_stream));
   Solver S{c, p};
   TRY(S.setup());
+  TRY(ensure_resident(c));
+  TRY(S.clear_ctl());
   const long long n = c->g.n;
   const int pinned = p->mode == SOCFV_PINNED;
   // g_P = w_out,P / (Q_out (s_eq - s_in)); Q_out from the outputs of the forward state
@@ -1050,18 +1105,19 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
     T *b[2] = {b0, b1};
     long long nb = S.nblk;
     int j = 0;
-    if constexpr (std::is_same_v<T, float>) {
-      if (dc && S.resident()) {
-        const int from = cc;
-        nb = S.launch_resident_sweeps(cc, k, true, gs, nullptr, nullptr);
-        HIPCHK(hipMemcpyAsync(&c->hctl->lost, &c->dctl->lost, sizeof(int), hipMemcpyDeviceToHost,
-                              c->st));
-        HIPCHK(hipGetLastError());
-        TRY(reduce_to_host(c, (int)nb, NV, 0u, out));
-        if (!c->hctl->lost) return 0;
-        cc = from;                       // given up: its input is as it was
-        c->res.C = 0;
+    if (S.resident<T>()) {
+      SweepArgs<T> a = S.sweep_args<T>(b[cc], b[cc ^ 1], dc, c->partial);
+      a.w = w;
+      a.gscale = (T)gs;
+      a.s_in = a.s_eq = T(0);            // nothing behind the inlet
+      bool ran;
+      TRY(S.resident_chunk<T>(a, k, true, out, ran));
+      if (ran) {
+        cc ^= 1;
+        return 0;
       }
+    }
+    if constexpr (std::is_same_v<T, float>) {
       // FP32 corrections: two transpose sweeps per launch where the shape allows; an odd
       // remainder ends with one single sweep
       if (dc && two_path(c->g) && S.t.two) {
@@ -1102,9 +1158,6 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
     }
   } else {
     rel = 1.0;
-    TRY(ensure_resident(c));
-    *c->hctl = SolveCtl{};
-    HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
     while (rel >= p->tol && S.it < p->max_iter) {
       launch_fill_f32(c->s32[0], n, 0.0f, c->st);
       launch_fill_f32(c->s32[1], n, 0.0f, c->st);

@@ -24,6 +24,7 @@
 // two-sweep kernel.
 #include "device.h"
 
+#include <iterator>
 #include <type_traits>
 
 namespace socfv {
@@ -128,6 +129,8 @@ __device__ __forceinline__ float open_of(float t) {
 __device__ __forceinline__ float coef_of(float t, float g) {
   return __builtin_amdgcn_fmed3f(t, g, 3.4e38f);
 }
+__device__ __forceinline__ double open_of(double t) { return fmin(fabs(t), 1.0); }
+__device__ __forceinline__ double coef_of(double t, double g) { return fmax(t, g); }
 
 // A column's coefficients in registers.
 template <typename T, int C, bool LEAN>
@@ -233,7 +236,7 @@ k_resident(SweepArgs<T> a, ResidentArgs p) {
   const int copy = stride * (Y + 2);
   vec *const lsrc = reinterpret_cast<vec *>(lds + (LEAN ? (copy + 3) / 4 * 4 : 0));
   vec *const ge = reinterpret_cast<vec *>(p.diag) + (long long)b * (C / NV16) * RT;
-  unsigned upd = 0;
+  unsigned upd = 0, pore = 0;
 #pragma unroll
   for (int k0 = 0; k0 < C; k0 += NV16) {
     vec ve, vsrc;
@@ -245,6 +248,7 @@ k_resident(SweepArgs<T> a, ResidentArgs p) {
       const Res1<T> r = resolve1<T>(a, p.adj, x, y, z0 + kc, i, pl);
       const T on = in ? T(1) : T(0);
       s[k] = in && !zero ? a.s[i] : T(0);
+      if (in && (a.flags[i] & FL_PORE)) pore |= 1u << k;
       q.axm[k] = in ? r.axm : T(0);
       q.axp[k] = in ? r.axp : T(0);
       q.aym[k] = in ? r.aym : T(0);
@@ -345,6 +349,7 @@ k_resident(SweepArgs<T> a, ResidentArgs p) {
   }
   __syncthreads();
 
+  const bool bound = !a.r0 && !p.adj;        // the state itself is swept: check its bounds
   double acc[NV] = {0, 0, 0, 0};
   T *rd = lds, *wr = NB == 2 ? lds + copy : lds;
   vec e0;                                    // diagonals of the next group
@@ -402,14 +407,15 @@ k_resident(SweepArgs<T> a, ResidentArgs p) {
         r = fma(azm, dn - c0, r);
         r = fma(azp, up - c0, r);
         if constexpr (LEAN && HELD)              // held cells keep their value
-          r = __builtin_bit_cast(T, __builtin_bit_cast(int, r) & ((int)(upd << (31 - k)) >> 31));
+          r = (int)(upd << (31 - k)) < 0 ? r : T(0);
         s[k] = fma(a.dt, r, c0);
         dn = c0;
         if (LAST) {
           const double rr = (double)r;
           acc[0] += rr * rr;
           acc[2] += rr;
-          if (!isfinite(rr)) acc[1] += 1.0;
+          if (!isfinite(rr) || (bound && (pore >> k & 1u) && !(s[k] >= a.lo && s[k] <= a.hi)))
+            acc[1] += 1.0;
         }
       }
       // finish the group here: sunk to where the values are used next, the arithmetic would keep
@@ -520,8 +526,8 @@ static int lds_bytes(int bytes, int C, int X, int Y) {
   return ((copy + 3) / 4 * 4 + RT * C) * bytes + columns * (int)sizeof(uint2);
 }
 
-// Cells per lane that the FP32 kernels are built for.
-constexpr int RES_C32[] = {4, 8, 12, 16, 20, 24, 32};
+// Cells per lane that the kernels are built for.
+constexpr int RES_C32[] = {4, 8, 12, 16, 20, 24, 32}, RES_C64[] = {2, 4, 8, 10, 12, 16};
 
 // Sub-boxes for a box of nx x ny x nz cells on ncu CUs: the split whose sweep the model below
 // takes shortest, or C = 0 if the box does not fit the chip.  The model, fitted to splits of
@@ -531,7 +537,10 @@ constexpr int RES_C32[] = {4, 8, 12, 16, 20, 24, 32};
 ResidentPlan resident_plan(const Grid &g, int bytes, int ncu) {
   ResidentPlan best{};
   double cost = 0;
-  for (const int C : RES_C32) {
+  const int *const Cs = bytes == 4 ? RES_C32 : RES_C64;
+  const int nC = bytes == 4 ? (int)std::size(RES_C32) : (int)std::size(RES_C64);
+  for (int ic = 0; ic < nC; ++ic) {
+    const int C = Cs[ic];
     const int gz = (g.nz + C - 1) / C;
     if (gz > ncu) continue;
     for (int gx = 1; gx * gz <= ncu && gx <= g.nx; ++gx) {
@@ -543,8 +552,8 @@ ResidentPlan resident_plan(const Grid &g, int bytes, int ncu) {
         const int lds = lds_bytes(bytes, C, X, Y), nj = resident_side_words(C);
         if (lds > RESIDENT_LDS || 2 * (X + Y) * C > nj * RT) continue;
         const int waves = (X * Y + 63) / 64;
-        const double words = (2.0 * (X + Y) * C + 2.0 * X * Y) * gx * gy * gz;
-        const double us = 1.0 + 0.03 * C * ((waves + 3) / 4) + 1.8e-6 * words +
+        const double words = (2.0 * (X + Y) * C + 2.0 * X * Y) * gx * gy * gz * (bytes / 4);
+        const double us = 1.0 + 0.0075 * bytes * C * ((waves + 3) / 4) + 1.8e-6 * words +
                           (resident_lean(bytes, C) ? 1.0 : 0.0);
         if (!best.C || us < cost) {
           cost = us;
@@ -593,9 +602,20 @@ void launch_resident(const SweepArgs<T> &a, const ResidentPlan &pl, const Reside
       case 24: go_resident<T, 24>(a, pl, p, st); break;
       default: go_resident<T, 32>(a, pl, p, st); break;
     }
+  } else {
+    switch (pl.C) {
+      case 2: go_resident<T, 2>(a, pl, p, st); break;
+      case 4: go_resident<T, 4>(a, pl, p, st); break;
+      case 8: go_resident<T, 8>(a, pl, p, st); break;
+      case 10: go_resident<T, 10>(a, pl, p, st); break;
+      case 12: go_resident<T, 12>(a, pl, p, st); break;
+      default: go_resident<T, 16>(a, pl, p, st); break;
+    }
   }
 }
 template void launch_resident<float>(const SweepArgs<float> &, const ResidentPlan &,
                                      const ResidentArgs &, hipStream_t);
+template void launch_resident<double>(const SweepArgs<double> &, const ResidentPlan &,
+                                      const ResidentArgs &, hipStream_t);
 
 }  // namespace socfv
