@@ -123,7 +123,7 @@ void socfv_default_params(socfv_params *p);
 /*
  * Geometry (pore / fibre voxels, the electrode's implicit-function description reduced to
  * voxels).  solid: device, uint8 (nz, ny, nx), nonzero = fibre voxel.  Builds the per-cell
- * flags (which faces touch fibre, pore bit) on the GPU and checks on the host that every
+ * flags (which faces touch fibre, pore bit) on the GPU and checks there that every
  * pore cell is face-connected to a pore cell of the inlet plane and that the outlet plane
  * has a pore cell (BAD_GEOMETRY otherwise).  *out receives a new context.
  */

@@ -258,6 +258,49 @@ int ensure_adjoint(socfv_ctx *c) {
   return 0;
 }
 
+// Pore cells not face-connected to the inlet plane, on the host (a breadth-first search): for
+// grids whose cells the GPU's 32-bit labels cannot number.
+int unconnected_on_host(socfv_ctx *c, long long *missing) {
+  const long long n = c->g.n, nx = c->g.nx, ny = c->g.ny, nz = c->g.nz;
+  std::vector<uint8_t> fl((size_t)n);
+  HIPCHK(hipMemcpyAsync(fl.data(), c->flags, (size_t)n, hipMemcpyDeviceToHost, c->st));
+  HIPCHK(hipStreamSynchronize(c->st));
+  std::vector<uint8_t> seen((size_t)n, 0);
+  std::vector<long long> queue;
+  queue.reserve((size_t)c->npore);
+  const long long pl = (long long)nx * ny;
+  for (long long z = 0; z < nz; ++z)
+    for (long long y = 0; y < ny; ++y) {
+      long long i = nx * (y + ny * z);
+      if (fl[i] & FL_PORE) { seen[i] = 1; queue.push_back(i); }
+    }
+  for (size_t h = 0; h < queue.size(); ++h) {
+    const long long i = queue[h];
+    const long long x = i % nx, y = (i / nx) % ny, z = i / pl;
+    const long long nb6[6] = {x > 0 ? i - 1 : -1, x < nx - 1 ? i + 1 : -1,
+                              y > 0 ? i - nx : -1, y < ny - 1 ? i + nx : -1,
+                              z > 0 ? i - pl : -1, z < nz - 1 ? i + pl : -1};
+    for (long long j : nb6)
+      if (j >= 0 && !seen[j] && (fl[j] & FL_PORE)) { seen[j] = 1; queue.push_back(j); }
+  }
+  *missing = c->npore - (long long)queue.size();
+  return 0;
+}
+
+// The same on the GPU.  The labels take the buffer that a solve's FP32 state will use.
+int unconnected(socfv_ctx *c, long long *missing) {
+  const long long n = c->g.n;
+  if (n >= (1ll << 31) - 1) return unconnected_on_host(c, missing);
+  if (!c->s32[0]) HIPCHK(hipMalloc(&c->s32[0], sizeof(int) * (size_t)(n + 1)));
+  const int nb = flags_blocks(c->g);
+  launch_connect(c->g, c->flags, (int *)c->s32[0], c->partial, nb, c->st);
+  HIPCHK(hipGetLastError());
+  double cnt = 0;
+  TRY(reduce_to_host(c, nb, 1, 0u, &cnt));
+  *missing = (long long)cnt;
+  return 0;
+}
+
 int check_params(const socfv_params *p) {
   if (!p) return fail(SOCFV_INVALID_ARG, "params is NULL");
   if (!(p->cfl > 0.0 && p->cfl <= 1.0)) return fail(SOCFV_INVALID_ARG, "cfl must be in (0, 1]");
@@ -859,30 +902,9 @@ int socfv_setup_geometry(socfv_ctx **out, int nx, int ny, int nz, const uint8_t 
   if (c->ninlet == 0 || c->noutlet == 0)
     return bail(fail(SOCFV_BAD_GEOMETRY, "no pore cell in the %s plane",
                      c->ninlet == 0 ? "inlet" : "outlet"));
-  // every pore cell must be face-connected to the inlet plane (host breadth-first search)
-  std::vector<uint8_t> fl((size_t)n);
-  if (hipMemcpyAsync(fl.data(), c->flags, (size_t)n, hipMemcpyDeviceToHost, c->st) != hipSuccess ||
-      hipStreamSynchronize(c->st) != hipSuccess)
-    return bail(fail(SOCFV_HIP_ERROR, "flags copy"));
-  std::vector<uint8_t> seen((size_t)n, 0);
-  std::vector<long long> queue;
-  queue.reserve((size_t)c->npore);
-  const long long pl = (long long)nx * ny;
-  for (long long z = 0; z < nz; ++z)
-    for (long long y = 0; y < ny; ++y) {
-      long long i = nx * (y + ny * z);
-      if (fl[i] & FL_PORE) { seen[i] = 1; queue.push_back(i); }
-    }
-  for (size_t h = 0; h < queue.size(); ++h) {
-    const long long i = queue[h];
-    const long long x = i % nx, y = (i / nx) % ny, z = i / pl;
-    const long long nb6[6] = {x > 0 ? i - 1 : -1, x < nx - 1 ? i + 1 : -1,
-                              y > 0 ? i - nx : -1, y < ny - 1 ? i + nx : -1,
-                              z > 0 ? i - pl : -1, z < nz - 1 ? i + pl : -1};
-    for (long long j : nb6)
-      if (j >= 0 && !seen[j] && (fl[j] & FL_PORE)) { seen[j] = 1; queue.push_back(j); }
-  }
-  const long long missing = c->npore - (long long)queue.size();
+  // every pore cell must be face-connected to the inlet plane
+  long long missing = 0;
+  if ((r = unconnected(c, &missing)) < 0) return bail(r);
   if (missing != 0)
     return bail(fail(SOCFV_BAD_GEOMETRY, "%lld pore cells are not face-connected to the inlet",
                      missing));

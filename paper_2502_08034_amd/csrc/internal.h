@@ -239,6 +239,11 @@ void launch_flags(const Grid &g, const uint8_t *solid, uint8_t *flags, double *p
                   int nblk, hipStream_t st);
 int flags_blocks(const Grid &g);
 
+// Pore cells not face-connected to the inlet plane: parent holds n + 1 ints (n < 2^31 - 1), one
+// partial (their count) per block of flags_blocks(g)
+void launch_connect(const Grid &g, const uint8_t *flags, int *parent, double *partial, int nblk,
+                    hipStream_t st);
+
 // velocity ingest: writes FP32 and FP64 per-cell lower faces and the outlet plane.
 // partial per block: [Q_in, max|div|, max|u|, bad-face count]
 void launch_velocity(const Grid &g, const uint8_t *flags, const double *ux, const double *uy,
@@ -284,7 +289,7 @@ void launch_outputs(const Grid &g, const uint8_t *flags, Faces<double> w, const 
                     double *partial, int nblk, hipStream_t st);
 int outputs_blocks(const Grid &g);
 
-// gradients (one thread per cell, flags_blocks(g) blocks): dU_dkappa and partial
+// gradients (flags_blocks(g) blocks): dU_dkappa and partial
 // [sum psi Radv, -, -, -]
 void launch_gradients(const Grid &g, const uint8_t *flags, Faces<double> w, const double *s,
                       const double *psi, double s_in, double s_eq, double Da, int pinned,

@@ -1,0 +1,62 @@
+"""Connectivity of the pore space on the GPU against SciPy's labelling (needs an MI355X).
+
+Random voxels near the percolation threshold (long, branching, mostly disconnected paths) on
+boxes around the kernels' 64-cell row segments and 256-cell blocks, and a winding channel whose
+single path visits every other row.  The count of unconnected cells is a whole number: equal.
+"""
+import re
+
+import numpy as np
+import pytest
+import torch
+from scipy import ndimage
+
+pytestmark = pytest.mark.gpu
+
+
+def unconnected(sv, solid):
+    """The count the library reports (0 if it accepts the geometry)."""
+    try:
+        sv.setup_geometry(torch.as_tensor(solid, device="cuda"))
+        return 0
+    except sv.SocfvError as e:
+        assert e.code == sv.BAD_GEOMETRY
+        return int(re.search(r"(\d+) pore cells", str(e)).group(1))
+
+
+def expected(solid):
+    lab, _ = ndimage.label(solid == 0)
+    inlet = np.unique(lab[:, :, 0])
+    return int(((lab > 0) & ~np.isin(lab, inlet[inlet > 0])).sum())
+
+
+@pytest.fixture(scope="module")
+def sv():
+    from paper_2502_08034_amd import socfv
+    assert torch.cuda.is_available()
+    return socfv
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(2, 1, 1), (63, 5, 4), (64, 5, 4), (65, 5, 4), (129, 17, 9),
+                                      (200, 30, 31), (7, 300, 11), (256, 64, 80)])
+@pytest.mark.parametrize("fill", [0.3, 0.65, 0.69, 0.8])
+def test_random_voxels(sv, nx, ny, nz, fill):
+    rng = np.random.Generator(np.random.PCG64(nx + 1000 * ny + int(100 * fill)))
+    solid = (rng.random((nz, ny, nx)) < fill).astype(np.uint8)
+    solid[0, 0, 0] = solid[-1, -1, -1] = 0          # a pore cell at the inlet and the outlet
+    assert unconnected(sv, solid) == expected(solid)
+
+
+@pytest.mark.parametrize("cut", [False, True])
+def test_winding_channel(sv, cut):
+    # rows y = 0, 2, 4, ... open from end to end, joined at alternating ends: one path
+    solid = np.ones((3, 41, 150), dtype=np.uint8)
+    solid[1, ::2, 1:] = 0
+    for k, y in enumerate(range(1, 41, 2)):
+        solid[1, y, -1 if k % 2 == 0 else 1] = 0
+    solid[1, 0, 0] = 0
+    if cut:
+        solid[1, 20, 75] = 1
+    want = expected(solid)
+    assert (want > 0) == cut
+    assert unconnected(sv, solid) == want
