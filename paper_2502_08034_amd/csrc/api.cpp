@@ -11,7 +11,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <deque>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -769,6 +768,163 @@ struct Solver {
     return status;
   }
 };
+
+// The resident part of a batched solve: every problem that fits the chip, several at a time, one
+// launch per chunk of K sweeps.  Which problems share a launch, and how many workgroups each gets,
+// is chosen anew after every read of the states: those with the most sweeps left first (from the
+// residual's decay), as many as fit at their fewest workgroups, then more workgroups to whichever
+// is slowest while any are left, so that a launch's problems end together.  On return h_ctl holds
+// every problem's state: CTL_RUN for one that does not fit, CTL_LOST for one whose launch was
+// given up; a problem's correction is in s32[0].
+int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver *S, int K,
+                   SolveCtl *d_ctl, SolveCtl *h_ctl, BatchProb *d_probs, double *d_out,
+                   hipStream_t bs) {
+  const int ncu = ctxs[0]->ncu;
+  std::vector<std::vector<ResidentPlan>> plans(n);
+  bool any = false;
+  for (int i = 0; i < n; ++i)
+    if (h_ctl[i].state == CTL_RUN && two_path(ctxs[i]->g) && !ctxs[i]->tiles_fixed) {
+      plans[i] = resident_plans(ctxs[i]->g, 4, ncu);
+      any = any || !plans[i].empty();
+    }
+  if (!any) return 0;
+  ResidentProb<float> *d_tab = nullptr;
+  int *d_of = nullptr;
+  unsigned long long *d_inbox = nullptr;
+  char *d_diag = nullptr;
+  double *d_part = nullptr;
+  const long long words = 2 * RESIDENT_BLOCK_WORDS * ncu;
+  const int rc = [&]() -> int {
+    if (hipMalloc(&d_tab, sizeof(ResidentProb<float>) * 2 * n) != hipSuccess ||
+        hipMalloc(&d_of, sizeof(int) * ncu) != hipSuccess ||
+        hipMalloc(&d_inbox, sizeof(unsigned long long) * words) != hipSuccess ||
+        hipMalloc(&d_diag, (size_t)RESIDENT_BLOCK_DIAG * ncu) != hipSuccess ||
+        hipMalloc(&d_part, sizeof(double) * NV * ncu) != hipSuccess) {
+      (void)hipGetLastError();
+      return 0;                          // no room: the tiled launches need less
+    }
+    launch_fill_f64((double *)d_inbox, words, 0.0, bs);
+    HIPCHK(hipGetLastError());
+    unsigned tag = 1;
+    std::vector<double> sweeps_left(n, 1e18);    // estimated
+    std::vector<long long> it_seen(n, 0);
+    std::vector<double> ri_seen(n, 0.0);
+    std::vector<ResidentProb<float>> tab(2 * n);
+    std::vector<BatchProb> hp;
+    std::vector<int> of(ncu);
+    for (;;) {
+      // the problems of the next launches, and their splits
+      std::vector<int> order, set;
+      for (int i = 0; i < n; ++i)
+        if (h_ctl[i].state == CTL_RUN && !plans[i].empty()) order.push_back(i);
+      if (order.empty()) break;
+      std::stable_sort(order.begin(), order.end(),
+                       [&](int a, int b) { return sweeps_left[a] > sweeps_left[b]; });
+      std::vector<size_t> pick(n, 0);
+      int used = 0;
+      for (int i : order)
+        if (used + plans[i][0].blocks() <= ncu) {
+          set.push_back(i);
+          used += plans[i][0].blocks();
+        }
+      for (;;) {
+        int slow = -1;
+        for (int i : set)
+          if (slow < 0 || plans[i][pick[i]].us > plans[slow][pick[slow]].us) slow = i;
+        if (pick[slow] + 1 >= plans[slow].size()) break;
+        const int more = plans[slow][pick[slow] + 1].blocks() - plans[slow][pick[slow]].blocks();
+        if (used + more > ncu) break;
+        ++pick[slow];
+        used += more;
+      }
+      hp.assign(n, BatchProb{});
+      for (int i = 0; i < n; ++i) hp[i].ctl = d_ctl + i;
+      int blk = 0, lds = 0;
+      for (size_t k = 0; k < set.size(); ++k) {
+        const int i = set[k];
+        socfv_ctx *c = ctxs[i];
+        const ResidentPlan &pl = plans[i][pick[i]];
+        BatchProb &b = hp[i];
+        b.gx = pl.gx; b.gy = pl.gy; b.gz = pl.gz;
+        b.tile0 = blk;
+        b.rpart = c->partial;
+        b.rnblk = march64_blocks(c->g);
+        for (int par = 0; par < 2; ++par) {
+          ResidentProb<float> &e = tab[par * n + k];
+          e = ResidentProb<float>{};
+          e.a = S[i].sweep_args<float>(c->s32[par], c->s32[par ^ 1], true,
+                                       d_part + (long long)NV * blk);
+          e.a.w = faces32(c);
+          e.a.gate = &d_ctl[i].state;
+          e.p.X = pl.X; e.p.Y = pl.Y; e.p.gx = pl.gx; e.p.gy = pl.gy; e.p.gz = pl.gz;
+          e.p.inbox = d_inbox + RESIDENT_BLOCK_WORDS * blk;
+          e.p.block_words = RESIDENT_BLOCK_WORDS;
+          e.p.slot_words = RESIDENT_BLOCK_WORDS * ncu;
+          e.p.diag = d_diag + RESIDENT_BLOCK_DIAG * blk;
+          e.p.abort = &d_ctl[i].lost;
+          e.p.limit = c->wait_limit;
+          e.p.fill = &d_ctl[i].fill;
+          e.blk0 = blk;
+          e.C = pl.C;
+        }
+        for (int t = 0; t < pl.blocks(); ++t) of[blk++] = (int)k;
+        lds = std::max(lds, pl.lds);
+      }
+      HIPCHK(hipMemcpyAsync(d_tab, tab.data(), sizeof(ResidentProb<float>) * 2 * n,
+                            hipMemcpyHostToDevice, bs));
+      HIPCHK(hipMemcpyAsync(d_of, of.data(), sizeof(int) * blk, hipMemcpyHostToDevice, bs));
+      HIPCHK(hipMemcpyAsync(d_probs, hp.data(), sizeof(BatchProb) * n, hipMemcpyHostToDevice, bs));
+      // chunks until the next read: up to four, not far beyond the first problem's end (its
+      // workgroups would idle)
+      double least = 1e18;
+      for (int i : set) least = std::min(least, sweeps_left[i]);
+      const int rounds = least > 1e17 ? 2 : (int)std::max(1.0, std::min(4.0, std::ceil(least / K)));
+      for (int r = 0; r < rounds; ++r) {
+        if (tag > 0xffffffffu - (unsigned)K) {
+          launch_fill_f64((double *)d_inbox, words, 0.0, bs);
+          tag = 1;
+        }
+        launch_resident_batch<float>(d_tab + (r & 1) * n, d_of, blk, lds, tag, K, bs);
+        tag += (unsigned)K;
+        launch_batch_reduce(d_probs, n, d_part, d_out, bs);
+        launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_CHUNK, d_out, K, bs);
+        for (int i : set) {
+          socfv_ctx *c = ctxs[i];
+          RefreshArgs a;
+          a.g = c->g; a.flags = c->flags; a.w = faces64(c); a.kappa = c->kappa;
+          a.s64 = nullptr; a.delta = c->s32[1]; a.s64_new = nullptr; a.r0 = c->r0;
+          a.s_in = p[i].s_in; a.s_eq = p[i].s_eq; a.Da = p[i].Da; a.pinned = S[i].pinned;
+          a.lo = S[i].lo; a.hi = S[i].hi; a.partial = c->partial; a.zc = S[i].t.zc;
+          launch_refresh_gated(a, c->s64[0], c->s64[1], d_ctl + i, bs);
+          std::swap(c->s32[0], c->s32[1]);       // the chunk's output is the next one's input
+        }
+        launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_REFRESH, nullptr, 0, bs);
+      }
+      HIPCHK(hipGetLastError());
+      HIPCHK(hipMemcpyAsync(h_ctl, d_ctl, sizeof(SolveCtl) * n, hipMemcpyDeviceToHost, bs));
+      HIPCHK(hipStreamSynchronize(bs));
+      for (int i : set) {
+        const SolveCtl &h = h_ctl[i];
+        if (h.state == CTL_DIVERGED)
+          return fail(SOCFV_DIVERGED, "batch problem %d diverged at sweep %lld", i, h.it);
+        if (h.state == CTL_LOST) {
+          // the first chunk that did not run read what the last one that ran wrote
+          const long long ran = (h.it - it_seen[i]) / K;
+          if ((rounds - ran) & 1) std::swap(ctxs[i]->s32[0], ctxs[i]->s32[1]);
+        }
+        if (ri_seen[i] > 0 && h.ri > 0 && h.ri < ri_seen[i] && h.it > it_seen[i])
+          sweeps_left[i] = std::log(p[i].tol / h.ri) * (double)(h.it - it_seen[i]) /
+                           std::log(h.ri / ri_seen[i]);
+        it_seen[i] = h.it;
+        ri_seen[i] = h.ri;
+      }
+    }
+    return 0;
+  }();
+  (void)hipStreamSynchronize(bs);
+  hfree(d_tab); hfree(d_of); hfree(d_inbox); hfree(d_diag); hfree(d_part);
+  return rc;
+}
 
 // outputs of state s: per-block partials at `partial` (outputs_blocks x NV2 doubles), the
 // reduced values at `dres` (NV2 doubles); both device memory the caller provides
@@ -1575,6 +1731,65 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       launch_fill_f32(c->s32[1], c->g.n, 0.0f, bs);
       if (res[i] < p[i].tol) { done[i] = 1; status[i] = SOCFV_OK; }
     }
+    // The device-side loop's state per problem.  One chunk is K sweeps, K a multiple of 4.
+    int K = 4;
+    for (int i = 0; i < n; ++i) K = std::max(K, S[i].chunk_len());
+    K = (K + 3) / 4 * 4;
+    HIPCHK(hipMalloc(&d_ctl, sizeof(SolveCtl) * n));
+    HIPCHK(hipHostMalloc(&h_ctl, sizeof(SolveCtl) * n, hipHostMallocDefault));
+    HIPCHK(hipMalloc(&d_probs, sizeof(BatchProb) * n));
+    HIPCHK(hipMalloc(&d_out, sizeof(double) * NV * n));
+    HIPCHK(hipHostMalloc(&h_out, sizeof(double) * NV * n, hipHostMallocDefault));
+    auto start_ctl = [&](int i) {
+      SolveCtl &h = h_ctl[i];
+      const long long it = h.it;
+      const int cycles = h.cycles;
+      h = SolveCtl{};
+      h.it = it;
+      h.cycles = cycles;
+      h.state = done[i] ? CTL_DONE : CTL_RUN;
+      h.fill = 0;                        // the corrections are zero
+      h.cur = cur[i];
+      h.max_iter = p[i].max_iter;
+      h.tol = p[i].tol;
+      h.tau = S[i].tau;
+      h.npore = (double)ctxs[i]->npore;
+      h.reduction = CYCLE_REDUCTION;
+      h.target = target[i];
+      h.best = INFINITY;
+      h.res = res[i];
+      h.ri = INFINITY;
+    };
+    for (int i = 0; i < n; ++i) {
+      h_ctl[i] = SolveCtl{};
+      start_ctl(i);
+    }
+    HIPCHK(hipMemcpyAsync(d_ctl, h_ctl, sizeof(SolveCtl) * n, hipMemcpyHostToDevice, bs));
+    HIPCHK(hipStreamSynchronize(bs));
+    TRY(batch_resident(n, ctxs, p, S.data(), K, d_ctl, h_ctl, d_probs, d_out, bs));
+    // what is left for the tiled launches: problems that do not fit the chip, and those whose
+    // resident launch was given up (their corrections go into the state first)
+    bool left = false;
+    for (int i = 0; i < n; ++i) {
+      done[i] = h_ctl[i].state != CTL_RUN && h_ctl[i].state != CTL_LOST;
+      if (h_ctl[i].state == CTL_LOST) {
+        socfv_ctx *c = ctxs[i];
+        cur[i] = h_ctl[i].cur;
+        res[i] = h_ctl[i].res;
+        if (!h_ctl[i].fill) {            // not at the start of a cycle
+          TRY(S[i].refresh(cur[i], cur[i] ^ 1, c->s32[0], out.data()));
+          cur[i] ^= 1;
+          res[i] = S[i].res_of(out[0]);
+          TRY(S[i].check(out.data(), res[i]));
+        }
+        target[i] = std::fmax(p[i].tol, CYCLE_REDUCTION * res[i]);
+        start_ctl(i);
+        if (res[i] < p[i].tol) done[i] = 1, h_ctl[i].state = CTL_DONE;
+      }
+      left = left || !done[i];
+    }
+    int bty = 4, bzc = 8;
+    if (left) {
     // Problems whose shape allows it (nx even; no activity field in the batch) take two
     // sweeps per launch in the batched two-sweep kernel; the others take the batched
     // single-sweep kernel.  Its block shape is picked by timing a few sweeps per candidate;
@@ -1592,8 +1807,6 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       tw[i] = two_w(g);
       trx[i] = pick_rx(g.nx, g.ny, tw[i]);
     }
-    HIPCHK(hipMalloc(&d_ctl, sizeof(SolveCtl) * n));
-    HIPCHK(hipHostMalloc(&h_ctl, sizeof(SolveCtl) * n, hipHostMallocDefault));
     int dev = 0, ncu = 256;
     HIPCHK(hipGetDevice(&dev));
     HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1670,7 +1883,6 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
           }
       zc2 = zc2_run;
     }
-    HIPCHK(hipMalloc(&d_probs, sizeof(BatchProb) * n));
     HIPCHK(hipMalloc(&d_tiles, sizeof(int) * max_tiles));
     // work lists: two-sweep items at d_work, single-sweep items at d_work + max_tiles;
     // their counts at d_nwork[0] and d_nwork[1]
@@ -1684,9 +1896,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       HIPCHK(hipMemcpy(d_grab, zero2, sizeof(int) * 2, hipMemcpyHostToDevice));
     }
     HIPCHK(hipMalloc(&d_part, sizeof(double) * NV * max_tiles));
-    HIPCHK(hipMalloc(&d_out, sizeof(double) * NV * n));
     HIPCHK(hipHostMalloc(&h_work, sizeof(int) * (2 * max_tiles + 2), hipHostMallocDefault));
-    HIPCHK(hipHostMalloc(&h_out, sizeof(double) * NV * n, hipHostMallocDefault));
     // work lists = every tile of the unfinished problems, by path (counts at h_work[0..1])
     auto upload_work = [&](const std::vector<BatchProb> &hp_, const std::vector<int> &done_) -> int {
       int m[2] = {0, 0};
@@ -1716,7 +1926,6 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     float best_ms = 1e30f;
-    int bty = 4, bzc = 8;
     auto nblocks_for = [&](int ty, size_t ntiles) {
       // persistent grid: the blocks that fit the chip at once, never more than the tiles
       long long per_cu = std::max(1, 2048 / (64 * ty));
@@ -1770,25 +1979,6 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
     // for (one gated launch per problem), and each refreshed problem's stop rule.  The host
     // replays the graph a few times between reads of the states, and re-tiles the remaining
     // problems when some have finished.
-    int K = 4;
-    for (int i = 0; i < n; ++i) K = std::max(K, S[i].chunk_len());
-    K = (K + 3) / 4 * 4;
-    for (int i = 0; i < n; ++i) {
-      SolveCtl &h = h_ctl[i];
-      h = SolveCtl{};
-      h.state = done[i] ? CTL_DONE : CTL_RUN;
-      h.fill = 0;                        // zeroed above
-      h.cur = cur[i];
-      h.max_iter = p[i].max_iter;
-      h.tol = p[i].tol;
-      h.tau = S[i].tau;
-      h.npore = (double)ctxs[i]->npore;
-      h.reduction = CYCLE_REDUCTION;
-      h.target = target[i];
-      h.best = INFINITY;
-      h.res = res[i];
-      h.ri = INFINITY;
-    }
     HIPCHK(hipMemcpyAsync(d_ctl, h_ctl, sizeof(SolveCtl) * n, hipMemcpyHostToDevice, bs));
     HIPCHK(hipStreamSynchronize(bs));
     HIPCHK(hipStreamBeginCapture(bs, hipStreamCaptureModeThreadLocal));
@@ -1861,6 +2051,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
         HIPCHK(hipMemcpyAsync(d_tiles, tp.data(), sizeof(int) * tp.size(), hipMemcpyHostToDevice, bs));
         planned = nact;
       }
+    }
     }
     for (int i = 0; i < n; ++i) {
       const SolveCtl &h = h_ctl[i];

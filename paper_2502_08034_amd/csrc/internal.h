@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include <vector>
 
 namespace socfv {
 
@@ -348,9 +349,16 @@ struct ResidentPlan {
   int gx, gy, gz;       // sub-boxes along x, y, z
   int lds;              // bytes of LDS per workgroup
   long long block_words, slot_words;   // exchange words per workgroup, and per slot
+  double us;            // modelled time per sweep
+  int blocks() const { return gx * gy * gz; }
 };
-// bytes: of a value (4 or 8)
+// The fastest split of a box over at most ncu workgroups (C = 0: it does not fit), and the splits
+// that are faster than every one with fewer workgroups; bytes: of a value (4 or 8)
 ResidentPlan resident_plan(const Grid &g, int bytes, int ncu);
+std::vector<ResidentPlan> resident_plans(const Grid &g, int bytes, int ncu);
+// Most exchange words and bytes of diagonals of any FP32 workgroup
+constexpr long long RESIDENT_BLOCK_WORDS = 8ll * RESIDENT_LANES;
+constexpr long long RESIDENT_BLOCK_DIAG = 32ll * RESIDENT_LANES * 4;
 // bytes of ResidentArgs::diag (0: not used by this plan)
 long long resident_diag_bytes(const ResidentPlan &pl, int bytes);
 struct ResidentArgs {
@@ -369,6 +377,19 @@ struct ResidentArgs {
 template <typename T>
 void launch_resident(const SweepArgs<T> &a, const ResidentPlan &pl, const ResidentArgs &args,
                      hipStream_t st);
+
+// One problem of a launch over several: its arguments (p without tag0 and K), first workgroup and
+// column length
+template <typename T>
+struct ResidentProb {
+  SweepArgs<T> a;
+  ResidentArgs p;
+  int blk0, C;
+};
+// workgroup g works for problem tab[of[g]]; lds: the most any of them needs
+template <typename T>
+void launch_resident_batch(const ResidentProb<T> *tab, const int *of, int nblocks, int lds,
+                           unsigned tag0, int K, hipStream_t st);
 
 // Static scratch of the allocation-free entry point: SCRATCH_DOUBLES doubles of device memory
 // per GPU.  scratch_address gives its device address on device dev (which must be current at

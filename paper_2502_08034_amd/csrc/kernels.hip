@@ -1762,7 +1762,12 @@ __global__ void __launch_bounds__(64) k_batch_ctl_chunk(const BatchProb *__restr
                                                         const double *__restrict__ out, int n,
                                                         int k) {
   const int i = blockIdx.x * 64 + threadIdx.x;
-  if (i >= n || probs[i].ctl->state != CTL_RUN) return;
+  // a problem without tiles took no part in this chunk
+  if (i >= n || probs[i].gx == 0 || probs[i].ctl->state != CTL_RUN) return;
+  if (probs[i].ctl->lost) {
+    probs[i].ctl->state = CTL_LOST;
+    return;
+  }
   ctl_after_chunk(probs[i].ctl, out[(long long)NV * i], out[(long long)NV * i + 1], k);
 }
 

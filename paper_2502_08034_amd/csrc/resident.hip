@@ -24,6 +24,7 @@
 // two-sweep kernel.
 #include "device.h"
 
+#include <algorithm>
 #include <iterator>
 #include <type_traits>
 
@@ -201,9 +202,10 @@ __device__ __forceinline__ Side side_of(int q, int X, int Y) {
   return q < X ? Side{2, q} : Side{3, q - X};
 }
 
+// K sweeps of workgroup b of one problem.
 template <typename T, int C, bool HELD>
-__global__ void __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_resident(SweepArgs<T> a, ResidentArgs p) {
+__device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const ResidentArgs &p,
+                                               const int b) {
   if (a.gate && *a.gate != CTL_RUN) return;
   constexpr int S = col_stride<T, C>(), NV16 = V16<T>::n, WN = Wire<T>::N;
   constexpr int NJ = resident_side_words(C), NONE = 0xffff;
@@ -214,7 +216,6 @@ k_resident(SweepArgs<T> a, ResidentArgs p) {
   T *lds = reinterpret_cast<T *>(lds_raw);
   const int nx = a.g.nx, ny = a.g.ny, nz = a.g.nz;
   const int X = p.X, Y = p.Y, tid = threadIdx.x;
-  const int b = xcd_tile(blockIdx.x, gridDim.x);
   const int gxy = p.gx * p.gy;
   const int bx = b % p.gx, by = (b / p.gx) % p.gy, bz = b / gxy;
   const int xe = min(X, nx - bx * X), ye = min(Y, ny - by * Y), ze = min(C, nz - bz * C);
@@ -512,7 +513,41 @@ k_resident(SweepArgs<T> a, ResidentArgs p) {
     for (int k = 0; k < C; ++k)
       if (k < ze) a.s_new[o + pl * k] = s[k];
   }
-  block_store<NV>(acc, 0u, a.partial + (long long)NV * blockIdx.x);
+  block_store<NV>(acc, 0u, a.partial + (long long)NV * b);
+}
+
+// Two waves per SIMD: 256 registers a lane.
+#define RESIDENT_KERNEL \
+  __global__ void __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+
+template <typename T, int C, bool HELD>
+RESIDENT_KERNEL k_resident(SweepArgs<T> a, ResidentArgs p) {
+  resident_block<T, C, HELD>(a, p, xcd_tile(blockIdx.x, gridDim.x));
+}
+
+// Workgroups of several problems in one launch: workgroup g works for problem of[g] of the table.
+// Each problem's columns have their own length.
+template <typename T>
+RESIDENT_KERNEL k_resident_batch(const ResidentProb<T> *__restrict__ tab,
+                                 const int *__restrict__ of, unsigned tag0, int K) {
+  const int g = xcd_tile(blockIdx.x, gridDim.x);
+  const ResidentProb<T> &e = tab[of[g]];
+  const SweepArgs<T> a = e.a;
+  ResidentArgs p = e.p;
+  p.tag0 = tag0;
+  p.K = K;
+  const int b = g - e.blk0;
+  if constexpr (sizeof(T) == 4) {
+    switch (e.C) {
+      case 4: resident_block<T, 4, false>(a, p, b); break;
+      case 8: resident_block<T, 8, false>(a, p, b); break;
+      case 12: resident_block<T, 12, false>(a, p, b); break;
+      case 16: resident_block<T, 16, false>(a, p, b); break;
+      case 20: resident_block<T, 20, false>(a, p, b); break;
+      case 24: resident_block<T, 24, true>(a, p, b); break;
+      default: resident_block<T, 32, true>(a, p, b); break;
+    }
+  }
 }
 
 }  // namespace
@@ -529,14 +564,12 @@ static int lds_bytes(int bytes, int C, int X, int Y) {
 // Cells per lane that the kernels are built for.
 constexpr int RES_C32[] = {4, 8, 12, 16, 20, 24, 32}, RES_C64[] = {2, 4, 8, 10, 12, 16};
 
-// Sub-boxes for a box of nx x ny x nz cells on ncu CUs: the split whose sweep the model below
-// takes shortest, or C = 0 if the box does not fit the chip.  The model, fitted to splits of
-// 65 thousand to 4.2 million cells (within a tenth): 1 us for the exchange's latency and the
-// barriers, 0.06 us per cell of a full block's columns, 1.8 us per million exchanged words, and
-// 1 us more for lean columns.
-ResidentPlan resident_plan(const Grid &g, int bytes, int ncu) {
-  ResidentPlan best{};
-  double cost = 0;
+// Every split of a box over at most ncu workgroups with its time per sweep.  The model, fitted
+// to splits of 65 thousand to 4.2 million cells (within a tenth): 1 us for the exchange's latency
+// and the barriers, 0.06 us per cell of a full block's columns (0.12 in FP64), 1.8 us per million
+// exchanged words, and 1 us more for lean columns.
+template <typename F>
+static void resident_splits(const Grid &g, int bytes, int ncu, F &&take) {
   const int *const Cs = bytes == 4 ? RES_C32 : RES_C64;
   const int nC = bytes == 4 ? (int)std::size(RES_C32) : (int)std::size(RES_C64);
   for (int ic = 0; ic < nC; ++ic) {
@@ -553,17 +586,33 @@ ResidentPlan resident_plan(const Grid &g, int bytes, int ncu) {
         if (lds > RESIDENT_LDS || 2 * (X + Y) * C > nj * RT) continue;
         const int waves = (X * Y + 63) / 64;
         const double words = (2.0 * (X + Y) * C + 2.0 * X * Y) * gx * gy * gz * (bytes / 4);
-        const double us = 1.0 + 0.0075 * bytes * C * ((waves + 3) / 4) + 1.8e-6 * words +
-                          (resident_lean(bytes, C) ? 1.0 : 0.0);
-        if (!best.C || us < cost) {
-          cost = us;
-          best = ResidentPlan{C, X, Y, gx, gy, gz, lds, (nj + 2ll) * RT * (bytes / 4), 0};
-          best.slot_words = best.block_words * gx * gy * gz;
-        }
+        ResidentPlan p{C, X, Y, gx, gy, gz, lds, (nj + 2ll) * RT * (bytes / 4), 0, 0.0};
+        p.slot_words = p.block_words * gx * gy * gz;
+        p.us = 1.0 + 0.0075 * bytes * C * ((waves + 3) / 4) + 1.8e-6 * words +
+               (resident_lean(bytes, C) ? 1.0 : 0.0);
+        take(p);
       }
     }
   }
+}
+
+ResidentPlan resident_plan(const Grid &g, int bytes, int ncu) {
+  ResidentPlan best{};
+  resident_splits(g, bytes, ncu, [&](const ResidentPlan &p) {
+    if (!best.C || p.us < best.us) best = p;
+  });
   return best;
+}
+
+std::vector<ResidentPlan> resident_plans(const Grid &g, int bytes, int ncu) {
+  std::vector<ResidentPlan> all, front;
+  resident_splits(g, bytes, ncu, [&](const ResidentPlan &p) { all.push_back(p); });
+  std::sort(all.begin(), all.end(), [](const ResidentPlan &p, const ResidentPlan &q) {
+    return p.blocks() != q.blocks() ? p.blocks() < q.blocks() : p.us < q.us;
+  });
+  for (const ResidentPlan &p : all)
+    if (front.empty() || p.us < 0.97 * front.back().us) front.push_back(p);
+  return front;
 }
 
 long long resident_diag_bytes(const ResidentPlan &pl, int bytes) {
@@ -613,6 +662,15 @@ void launch_resident(const SweepArgs<T> &a, const ResidentPlan &pl, const Reside
     }
   }
 }
+template <typename T>
+void launch_resident_batch(const ResidentProb<T> *tab, const int *of, int nblocks, int lds,
+                           unsigned tag0, int K, hipStream_t st) {
+  const int bytes = lds > RESIDENT_LDS_ALONE ? lds : RESIDENT_LDS_ALONE;
+  k_resident_batch<T><<<nblocks, RT, bytes, st>>>(tab, of, tag0, K);
+}
+template void launch_resident_batch<float>(const ResidentProb<float> *, const int *, int, int,
+                                           unsigned, int, hipStream_t);
+
 template void launch_resident<float>(const SweepArgs<float> &, const ResidentPlan &,
                                      const ResidentArgs &, hipStream_t);
 template void launch_resident<double>(const SweepArgs<double> &, const ResidentPlan &,

@@ -132,3 +132,52 @@ def test_resident_fp64_sweeps_equal_the_march(sv, shape, kappa, mode):
     assert (s1 - s2).abs().max() <= 1e-12
     assert (a1 - a2).abs().max() <= 1e-12 * a2.abs().max()
     assert abs(r1.residual - r2.residual) <= 1e-9 * r2.residual
+
+
+def batch_of(sv, shapes):
+    return [problem(sv, inputs_of(shape, kappa)) for shape, kappa in shapes]
+
+
+BATCH = [((64, 32, 33), False), ((131, 33, 41), True), ((129, 63, 65), False),
+         ((45, 20, 17), False), ((96, 80, 77), True)]
+
+
+def test_batched_resident_sweeps_equal_the_single_solves(sv):
+    # problems with and without an activity field, finite and pinned, one with a cap on its
+    # sweeps: the same states as alone (the FP32 sweeps bit for bit, the polish to its rounding)
+    pbs = batch_of(sv, BATCH)
+    ps = [sv.params(precision="fp32", tol=1e-9, **(PINNED if k == 2 else FINITE))
+          for k in range(len(pbs))]
+    ps[3].max_iter = 600
+    states, stats = sv.batch_solve([pb.ctx for pb in pbs], ps)
+    for k, (pb, p, s, st) in enumerate(zip(pbs, ps, states, stats)):
+        r, rt = sv.solve_soc_steady(pb.ctx, p)
+        assert st.status == rt.status == (sv.NOT_CONVERGED if k == 3 else sv.OK), k
+        assert st.iterations == rt.iterations and st.cycles == rt.cycles, k
+        assert (s - r).abs().max() <= 1e-12, k
+
+
+def test_a_batch_beyond_the_chip_runs_in_turns(sv):
+    # more cells than the chip holds at once (four boxes of 1.4 million)
+    inputs = inputs_of((175, 89, 89))
+    pbs = [problem(sv, inputs) for _ in range(4)]
+    p = sv.params(precision="fp32", tol=1e-6, **FINITE)
+    states, stats = sv.batch_solve([pb.ctx for pb in pbs], [p] * 4)
+    s, st = sv.solve_soc_steady(pbs[0].ctx, p)
+    for x, xt in zip(states, stats):
+        assert xt.status == sv.OK and xt.iterations == st.iterations
+        assert (x - s).abs().max() <= 1e-12
+
+
+def test_a_batch_whose_launches_are_given_up_still_converges(sv):
+    # wait limit 0 on two of the problems: they go on in the tiled launches, from a state that
+    # the correction so far has gone into; the fixed point is the same
+    pbs = batch_of(sv, BATCH)
+    p = [sv.params(precision="fp32", tol=1e-9, **FINITE) for _ in pbs]
+    for k in (0, 4):
+        sv.set_wait_limit(pbs[k].ctx, 0.0)
+    states, stats = sv.batch_solve([pb.ctx for pb in pbs], p)
+    for pb, q, s, st in zip(pbs, p, states, stats):
+        assert st.status == sv.OK and st.residual < 1e-9
+        r, _ = sv.solve_soc_steady(pb.ctx, q)
+        assert (s - r).abs().max() <= 1e-7          # both within the tolerance of the fixed point
