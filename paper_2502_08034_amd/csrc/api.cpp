@@ -2236,6 +2236,18 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     double **cellv[6] = {&a.p, &a.r, &a.z, &a.q, &a.d[0], &a.d[1]};
     for (double **v : cellv) TRY(alloc((void **)v, sizeof(double) * (size_t)n));
     TRY(alloc((void **)&a.ccode, (size_t)n));
+    {
+      std::vector<int> order(a.nbc + 3 * a.nbf);
+      flow_order((long long)g.nx * g.ny, a.nbc, order.data());
+      flow_order((long long)(g.nx + 1) * g.ny, a.nbf, order.data() + a.nbc);
+      flow_order((long long)g.nx * (g.ny + 1), a.nbf, order.data() + a.nbc + a.nbf);
+      flow_order((long long)g.nx * g.ny, a.nbf, order.data() + a.nbc + 2 * a.nbf);
+      TRY(alloc((void **)&a.corder, sizeof(int) * order.size()));
+      for (int k = 0; k < 3; ++k) a.forder[k] = a.corder + a.nbc + k * a.nbf;
+      HIPCHK(hipMemcpyAsync(a.corder, order.data(), sizeof(int) * order.size(),
+                            hipMemcpyHostToDevice, c->st));
+      HIPCHK(hipStreamSynchronize(c->st));
+    }
     const long long npart = 6ll * a.nbc + 6ll * a.nbf + 4ll * a.nbc + FS_N;
     double *part = nullptr;
     TRY(alloc((void **)&part, sizeof(double) * (size_t)npart));
@@ -2263,16 +2275,45 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     long steps = 0;
     double total_prev = 0.0, du = INFINITY, un = 0.0;
     int m = p->cg_max;
+    int guess = 16, from = -1;           // CG iterations to enqueue; where a stalled CG goes on
+    double seen = 0.0;
+    long group = 1;                      // steps to enqueue
+    const long most = n > (1 << 19) ? 1 : 4;   // (a large box's step hides the read)
     int status = SOCFV_NOT_CONVERGED;
     while (steps < p->max_steps) {
       const long k = std::min<long>(p->check_every, p->max_steps - steps);
-      for (long s = 0; s < k; ++s) {
-        launch_flow_predict(a, c->st);
-        launch_flow_cg_init(a, c->st);
-        for (int j = 0; j < m; ++j) launch_flow_cg_iter(a, j, c->st);
-        launch_flow_project(a, c->st);
+      // The steps are enqueued a few at a time with as many CG iterations each as the last ones
+      // took and some more (a launch past a CG's end returns at once but costs about 2 us); a
+      // step that needs more stalls what follows, and the read after the group resumes it.
+      for (long s = 0; s < k;) {
+        const long grp = std::min<long>(k - s, group);
+        for (long q = 0; q < grp; ++q) {
+          if (q > 0 || from < 0) {
+            launch_flow_predict(a, c->st);
+            launch_flow_cg_init(a, c->st);
+          }
+          const int j0 = q == 0 && from > 0 ? from : 0;
+          for (int j = j0; j < std::min(m, j0 + guess); ++j) launch_flow_cg_iter(a, j, c->st);
+          launch_flow_project(a, m, c->st);
+        }
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(c->hres, a.sc, sizeof(double) * FS_N, hipMemcpyDeviceToHost, c->st));
+        HIPCHK(hipStreamSynchronize(c->st));
+        const long ran = (long)c->hres[FS_STEPS] - steps - s;
+        s += ran;
+        if (c->hres[FS_STALL] != 0.0) {
+          from = (int)c->hres[FS_CG_STEP];
+          guess = std::max(8, from / 2);
+          group = 1;
+          launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
+        } else {
+          from = -1;
+          const int next = (int)std::ceil(1.2 * (c->hres[FS_CG_TOTAL] - seen) / (double)ran) + 3;
+          group = 2 * next < guess ? 1 : std::min(2 * group, most);   // a step of many: alone
+          guess = next;
+        }
+        seen = c->hres[FS_CG_TOTAL];
       }
-      HIPCHK(hipGetLastError());
       launch_reduce(a.pdu, 3 * a.nbf, 2, 0u, c->dres, c->st);
       HIPCHK(hipGetLastError());
       HIPCHK(hipMemcpyAsync(c->hres, c->dres, sizeof(double) * 2, hipMemcpyDeviceToHost, c->st));
@@ -2285,8 +2326,7 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
       const double total = c->hres[2];
       if (!std::isfinite(du) || !std::isfinite(un))
         return fail(SOCFV_DIVERGED, "flow steps diverged at step %ld", steps);
-      // launch enough CG iterations for this phase: twice the recent average plus 4, at
-      // least 8 (kernels past the stop return at once, at about 2 us each)
+      // cap of this phase's CG: twice the recent average plus 4, at least 8
       const double avg = (total - total_prev) / (double)k;
       total_prev = total;
       m = std::min(p->cg_max, std::max(8, (int)std::ceil(2.0 * avg) + 4));

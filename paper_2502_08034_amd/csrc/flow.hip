@@ -23,6 +23,9 @@
 // order, so all blocks take the same (deterministic) values and the same stop decision.
 #include "internal.h"
 
+#include <algorithm>
+#include <vector>
+
 namespace socfv {
 
 namespace {
@@ -73,12 +76,14 @@ __device__ __forceinline__ double sum_partials(const double *a, int n, int strid
   return block_total(v, false, sh);
 }
 
-// Workgroups go to the eight XCDs in turn (block b to XCD b % 8), each XCD with its own L2.
-// Renumbering them so that every XCD works one contiguous run of logical blocks keeps a
-// cell's row neighbours (the next block) in the same L2.  A bijection on [0, nb).
-__device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
-  const unsigned x = b % 8u, k = b / 8u, q = nb / 8u, r = nb % 8u;
-  return x * q + (x < r ? x : r) + k;
+// The logical block of a workgroup (flow_order), and the place of its partials: a block's own,
+// so that every sum is taken in one order whichever workgroup does the work.
+struct Logical {
+  unsigned lb, slot;
+};
+__device__ __forceinline__ Logical logical(const int *__restrict__ order) {
+  const unsigned o = (unsigned)order[blockIdx.x];
+  return {o & 0xffffu, o >> 16};
 }
 
 __device__ __forceinline__ bool pore_at(const uint8_t *fl, const Grid &g, int x, int y, int z) {
@@ -156,10 +161,11 @@ __device__ __forceinline__ double nb_sum(const double *__restrict__ v, long long
 // ---- face classification ---------------------------------------------------------------
 __global__ void __launch_bounds__(FB) k_flow_codes(FlowArgs a) {
   const Grid g = a.g;
+  const Logical me = logical(a.forder[blockIdx.y]);
   const int o = blockIdx.y;
   const FaceDims d = face_dims(g, o);
   uint16_t *code = a.code[o];
-  for (long long f = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; f < d.n;
+  for (long long f = (long long)me.lb * FB + threadIdx.x; f < d.n;
        f += (long long)gridDim.x * FB) {
     const unsigned fu = (unsigned)f, t = fu / (unsigned)d.fx;
     const int x = (int)(fu - t * (unsigned)d.fx);
@@ -184,7 +190,8 @@ __global__ void __launch_bounds__(FB) k_flow_codes(FlowArgs a) {
 
 __global__ void __launch_bounds__(FB) k_flow_cell_codes(FlowArgs a) {
   const Grid g = a.g;
-  for (long long c = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; c < g.n;
+  const Logical me = logical(a.corder);
+  for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
        c += (long long)gridDim.x * FB) {
     const uint8_t fl = a.flags[c];
     unsigned cc = 0;
@@ -200,7 +207,9 @@ __global__ void __launch_bounds__(FB) k_flow_cell_codes(FlowArgs a) {
 
 // ---- predictor: u* = u + dt L u ----------------------------------------------------------
 __global__ void __launch_bounds__(FB) k_flow_predict(FlowArgs a) {
+  if (a.sc[FS_STALL] != 0.0) return;
   const Grid g = a.g;
+  const Logical me = logical(a.forder[blockIdx.y]);
   const int o = blockIdx.y;
   const FaceDims d = face_dims(g, o);
   const uint16_t *__restrict__ code = a.code[o];
@@ -208,7 +217,7 @@ __global__ void __launch_bounds__(FB) k_flow_predict(FlowArgs a) {
   double *__restrict__ us = a.us[o];
   const long long off[6] = {-1, 1, -(long long)d.fx, (long long)d.fx,
                             -(long long)d.fx * d.fy, (long long)d.fx * d.fy};
-  for (long long f = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; f < d.n;
+  for (long long f = (long long)me.lb * FB + threadIdx.x; f < d.n;
        f += (long long)gridDim.x * FB) {
     const unsigned c = code[f];
     double out = 0.0;
@@ -236,7 +245,9 @@ __global__ void __launch_bounds__(FB) k_flow_predict(FlowArgs a) {
 // parity 0.  Block 0 also sets the step's stop target from the last projection's partials.
 __global__ void __launch_bounds__(FB) k_flow_cg_init(FlowArgs a) {
   __shared__ double sh[FB / 64];
+  if (a.sc[FS_STALL] != 0.0) return;
   const Grid g = a.g;
+  const Logical me = logical(a.corder);
   if (blockIdx.x == 0) {
     const double du2 = sum_partials(a.pdu, 3 * a.nbf, 2, sh);
     if (threadIdx.x == 0) {
@@ -247,7 +258,7 @@ __global__ void __launch_bounds__(FB) k_flow_cg_init(FlowArgs a) {
   }
   const long long sy = g.nx, sz = (long long)g.nx * g.ny;
   double rz = 0.0, rr = 0.0, fl = 0.0;
-  for (long long c = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; c < g.n;
+  for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
        c += (long long)gridDim.x * FB) {
     const unsigned cc = a.ccode[c];
     double rv = 0.0, zv = 0.0;
@@ -275,9 +286,9 @@ __global__ void __launch_bounds__(FB) k_flow_cg_init(FlowArgs a) {
   rr = block_total(rr, false, sh);
   fl = block_total(fl, false, sh);
   if (threadIdx.x == 0) {
-    a.prz[0][blockIdx.x] = rz;
-    a.prr[0][blockIdx.x] = rr;
-    a.pfl[blockIdx.x] = fl;
+    a.prz[0][me.slot] = rz;
+    a.prr[0][me.slot] = rr;
+    a.pfl[me.slot] = fl;
   }
 }
 
@@ -291,8 +302,9 @@ constexpr double CG_FLOOR = 16.0;
 // iteration j, first half: stop test; d = z + beta d_old; q = A d; partials of d.q
 __global__ void __launch_bounds__(FB) k_flow_cg_a(FlowArgs a, int j) {
   __shared__ double sh[FB / 64];
-  if (a.sc[FS_DONE] != 0.0) return;
+  if (a.sc[FS_DONE] != 0.0 || a.sc[FS_STALL] != 0.0) return;
   const Grid g = a.g;
+  const Logical me = logical(a.corder);
   const int par = j & 1;
   const double rz = sum_partials(a.prz[par], a.nbc, 1, sh);
   const double rr = sum_partials(a.prr[par], a.nbc, 1, sh);
@@ -308,7 +320,7 @@ __global__ void __launch_bounds__(FB) k_flow_cg_a(FlowArgs a, int j) {
   double *__restrict__ dn = a.d[par];
   const long long sy = g.nx, sz = (long long)g.nx * g.ny;
   double dq = 0.0;
-  for (long long c = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; c < g.n;
+  for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
        c += (long long)gridDim.x * FB) {
     const unsigned cc = a.ccode[c];
     double dv = 0.0, qv = 0.0;
@@ -329,22 +341,23 @@ __global__ void __launch_bounds__(FB) k_flow_cg_a(FlowArgs a, int j) {
     a.q[c] = qv;
   }
   dq = block_total(dq, false, sh);
-  if (threadIdx.x == 0) a.pdq[blockIdx.x] = dq;
+  if (threadIdx.x == 0) a.pdq[me.slot] = dq;
 }
 
 // iteration j, second half: alpha = r.z / d.q; p += alpha d; r -= alpha q; z = r / diag;
 // partials of the new r.z, r.r into the other parity
 __global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j) {
   __shared__ double sh[FB / 64];
-  if (a.sc[FS_DONE] != 0.0) return;
+  if (a.sc[FS_DONE] != 0.0 || a.sc[FS_STALL] != 0.0) return;
   const Grid g = a.g;
+  const Logical me = logical(a.corder);
   const int par = j & 1;
   const double rz = sum_partials(a.prz[par], a.nbc, 1, sh);
   const double dq = sum_partials(a.pdq, a.nbc, 1, sh);
   const double alpha = rz / dq;
   const double *__restrict__ dn = a.d[par];
   double rzn = 0.0, rrn = 0.0;
-  for (long long c = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; c < g.n;
+  for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
        c += (long long)gridDim.x * FB) {
     const unsigned cc = a.ccode[c];
     if (!cc) continue;
@@ -360,16 +373,25 @@ __global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j) {
   rzn = block_total(rzn, false, sh);
   rrn = block_total(rrn, false, sh);
   if (threadIdx.x == 0) {
-    a.prz[par ^ 1][blockIdx.x] = rzn;
-    a.prr[par ^ 1][blockIdx.x] = rrn;
+    a.prz[par ^ 1][me.slot] = rzn;
+    a.prr[par ^ 1][me.slot] = rrn;
     if (blockIdx.x == 0) a.sc[FS_CG_STEP] = (double)(j + 1);
   }
 }
 
 // ---- projection: u' = u* - dt (G p + gbc); partials [sum (u' - u)^2, sum u'^2] -----------
-__global__ void __launch_bounds__(FB) k_flow_project(FlowArgs a) {
+// A step whose CG has neither met its target nor reached the cap has run out of launched
+// iterations: nothing is projected, and the launches behind this one return until the host has
+// enqueued more (the decision is the same in every block: none writes what it reads).
+__global__ void __launch_bounds__(FB) k_flow_project(FlowArgs a, int cap) {
   __shared__ double sh[FB / 64];
+  if (a.sc[FS_STALL] != 0.0) return;
+  if (a.sc[FS_DONE] == 0.0 && a.sc[FS_CG_STEP] < (double)cap) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.sc[FS_STALL] = 1.0;
+    return;
+  }
   const Grid g = a.g;
+  const Logical me = logical(a.forder[blockIdx.y]);
   const int o = blockIdx.y;
   const FaceDims d = face_dims(g, o);
   const uint16_t *__restrict__ code = a.code[o];
@@ -377,7 +399,7 @@ __global__ void __launch_bounds__(FB) k_flow_project(FlowArgs a) {
   double *__restrict__ u = a.u[o];
   const double *__restrict__ p = a.p;
   double du2 = 0.0, u2 = 0.0;
-  for (long long f = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; f < d.n;
+  for (long long f = (long long)me.lb * FB + threadIdx.x; f < d.n;
        f += (long long)gridDim.x * FB) {
     double un = 0.0;
     if (code[f] & FC_OPEN) {
@@ -407,10 +429,13 @@ __global__ void __launch_bounds__(FB) k_flow_project(FlowArgs a) {
   du2 = block_total(du2, false, sh);
   u2 = block_total(u2, false, sh);
   if (threadIdx.x == 0) {
-    const long long b = (long long)o * a.nbf + blockIdx.x;
+    const long long b = (long long)o * a.nbf + me.slot;
     a.pdu[2 * b] = du2;
     a.pdu[2 * b + 1] = u2;
-    if (o == 0 && blockIdx.x == 0) a.sc[FS_CG_TOTAL] += a.sc[FS_CG_STEP];
+    if (o == 0 && blockIdx.x == 0) {
+      a.sc[FS_CG_TOTAL] += a.sc[FS_CG_STEP];
+      a.sc[FS_STEPS] += 1.0;
+    }
   }
 }
 
@@ -418,9 +443,10 @@ __global__ void __launch_bounds__(FB) k_flow_project(FlowArgs a) {
 __global__ void __launch_bounds__(FB) k_flow_check(FlowArgs a) {
   __shared__ double sh[FB / 64];
   const Grid g = a.g;
+  const Logical me = logical(a.corder);
   const long long sz = (long long)g.nx * g.ny;
   double dmax = 0.0, qin = 0.0, umax = 0.0, qout = 0.0;
-  for (long long c = (long long)xcd_block(blockIdx.x, gridDim.x) * FB + threadIdx.x; c < g.n;
+  for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
        c += (long long)gridDim.x * FB) {
     const unsigned cc = a.ccode[c];
     if (!cc) continue;
@@ -439,7 +465,7 @@ __global__ void __launch_bounds__(FB) k_flow_check(FlowArgs a) {
   umax = block_total(umax, true, sh);
   qout = block_total(qout, false, sh);
   if (threadIdx.x == 0) {
-    double *o = a.pdiv + 4ll * blockIdx.x;
+    double *o = a.pdiv + 4ll * me.slot;
     o[0] = dmax;
     o[1] = qin;
     o[2] = umax;
@@ -460,6 +486,33 @@ int flow_face_blocks(const Grid &g) {
   return (int)(b < FLOW_MAX_BLOCKS ? b : FLOW_MAX_BLOCKS);
 }
 
+// Order of the logical blocks.  Workgroup b runs on XCD b % 8, each XCD with its own L2, and the
+// blocks' window (256 nb cells) moves through the box plane by plane.  A logical block's place in
+// its plane decides its XCD: each gets a band of rows over all the window's planes, so that a
+// cell's z neighbours are always in the L2 that reads it and only the rows at a band's edges are
+// read by two.  With runs of consecutive blocks per XCD (two planes each on 256 x 128 x 128) every
+// XCD read its neighbours' planes too: 47 us for the first half of a CG iteration against
+// 43 here.  order[b]: workgroup b's logical block, and << 16 the place of its partials: the
+// sums run over the blocks eight apart (0, nb / 8, ... the runs' first blocks, then their second
+// ones), the order in which workgroups took consecutive runs.  Bijections on [0, nb).
+void flow_order(long long plane, int nb, int *order) {
+  std::vector<int> lb(nb), slot(nb);
+  for (int k = 0; k < nb; ++k) lb[k] = k;
+  for (int b = 0; b < nb; ++b) {
+    const int x = b % 8, k = b / 8;
+    slot[x * (nb / 8) + std::min(x, nb % 8) + k] = b;
+  }
+  const auto place = [&](int k) { return (long long)FB * k % plane; };
+  std::stable_sort(lb.begin(), lb.end(), [&](int a, int b) { return place(a) < place(b); });
+  int at = 0;
+  for (int x = 0; x < 8; ++x) {
+    const int n = nb / 8 + (x < nb % 8 ? 1 : 0);
+    std::sort(lb.begin() + at, lb.begin() + at + n);
+    for (int k = 0; k < n; ++k) order[8 * k + x] = lb[at + k] | slot[lb[at + k]] << 16;
+    at += n;
+  }
+}
+
 void launch_flow_codes(const FlowArgs &a, hipStream_t st) {
   k_flow_codes<<<dim3(a.nbf, 3), FB, 0, st>>>(a);
   k_flow_cell_codes<<<a.nbc, FB, 0, st>>>(a);
@@ -474,8 +527,8 @@ void launch_flow_cg_iter(const FlowArgs &a, int j, hipStream_t st) {
   k_flow_cg_a<<<a.nbc, FB, 0, st>>>(a, j);
   k_flow_cg_b<<<a.nbc, FB, 0, st>>>(a, j);
 }
-void launch_flow_project(const FlowArgs &a, hipStream_t st) {
-  k_flow_project<<<dim3(a.nbf, 3), FB, 0, st>>>(a);
+void launch_flow_project(const FlowArgs &a, int cap, hipStream_t st) {
+  k_flow_project<<<dim3(a.nbf, 3), FB, 0, st>>>(a, cap);
 }
 void launch_flow_check(const FlowArgs &a, hipStream_t st) {
   k_flow_check<<<a.nbc, FB, 0, st>>>(a);

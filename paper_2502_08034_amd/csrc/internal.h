@@ -196,7 +196,10 @@ void launch_nernst(const NernstArgs &a, const Tiles &t, hipStream_t st);
 // outlet plane (zero gradient), 1 open, 2 closed along the face normal, 3 wall across it.
 constexpr uint16_t FC_OPEN = 0x8000;
 // Scalar slots of the flow step (device doubles after the partials)
-enum FlowSlot { FS_TARGET = 0, FS_DONE = 1, FS_CG_STEP = 2, FS_CG_TOTAL = 3, FS_N = 4 };
+// (FS_DONE: the step's CG met its target; FS_CG_STEP its iterations; FS_STALL: a step ran out of
+// launched CG iterations, and everything enqueued after it returns at once)
+enum FlowSlot { FS_TARGET = 0, FS_DONE = 1, FS_CG_STEP = 2, FS_CG_TOTAL = 3, FS_STEPS = 4,
+                FS_STALL = 5, FS_N = 6 };
 struct FlowArgs {
   Grid g;
   const uint8_t *flags;
@@ -207,6 +210,7 @@ struct FlowArgs {
   double *p, *r, *z, *q, *d[2];   // pressure and CG vectors (cells)
   double dt, p_in, theta2;        // theta2: (CG stop factor)^2
   int nbc, nbf;          // blocks of the cell kernels / per face array of the face kernels
+  int *corder, *forder[3];        // logical block of each workgroup (flow_order)
   double *prz[2], *prr[2], *pdq;  // per-block CG partials (cell kernels), ping-pong by parity
   double *pdu;           // per-block [sum du^2, sum u^2] of the projection, (3 nbf) x 2
   double *pdiv;          // per-block [max |div u|, inlet flux] (cell kernels), nbc x 2
@@ -215,11 +219,14 @@ struct FlowArgs {
 };
 int flow_cell_blocks(const Grid &g);
 int flow_face_blocks(const Grid &g);
+// plane: cells or faces of one z plane
+void flow_order(long long plane, int nb, int *order);
 void launch_flow_codes(const FlowArgs &a, hipStream_t st);
 void launch_flow_predict(const FlowArgs &a, hipStream_t st);
 void launch_flow_cg_init(const FlowArgs &a, hipStream_t st);
 void launch_flow_cg_iter(const FlowArgs &a, int j, hipStream_t st);   // both CG kernels
-void launch_flow_project(const FlowArgs &a, hipStream_t st);
+// cap: CG iterations after which a step goes on without having met its target
+void launch_flow_project(const FlowArgs &a, int cap, hipStream_t st);
 void launch_flow_check(const FlowArgs &a, hipStream_t st);   // fills pdiv
 
 

@@ -154,3 +154,18 @@ def test_resume_continues_the_iteration(sv):
     assert resumed[4].steps == 20 and resumed[4].status == sv.NOT_CONVERGED
     for got, want in zip(resumed[:4], full[:4]):
         assert torch.equal(got, want)
+
+
+def test_cg_cap_and_stalled_steps(sv):
+    # CG iterations are enqueued from the last steps' count: a target no CG reaches makes every
+    # step run to the cap (far above the first guess), one that every CG starts below needs none
+    # after the first step, and both leave a flow that later steps continue
+    g = I.fibres_nonoverlap(32, 16, 16, 2.5, 0.85, 3)
+    ctx = sv.setup_geometry(torch.as_tensor(g.solid, device="cuda"))
+    for cap in (1, 15, 16, 17, 90):
+        st = sv.solve_stokes(ctx, cfl=2.0, max_steps=11, check_every=11, cg_theta=1e-200,
+                             cg_max=cap, tol=0.0)[4]
+        assert st.steps == 11 and 0 < st.cg_iterations <= 11 * cap
+        assert cap > 17 or st.cg_iterations == 11 * cap
+    st = sv.solve_stokes(ctx, cfl=2.0, max_steps=9, cg_theta=1e30, cg_max=40, tol=0.0)[4]
+    assert st.steps == 9 and st.cg_iterations <= 40
