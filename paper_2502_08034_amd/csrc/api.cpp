@@ -90,7 +90,7 @@ struct socfv_ctx {
   bool tiles_fixed = false;
   // resident sweeps: the box's FP32 and FP64 splits (C = 0: none), their exchange words and the
   // next tag
-  ResidentPlan res{}, res64{};
+  ResidentPlan res{}, res64{}, resn{};   // (resn: the Nernst iteration's)
   bool res_planned = false;
   unsigned long long *inbox = nullptr;
   void *res_diag = nullptr;
@@ -223,12 +223,13 @@ int ensure_resident(socfv_ctx *c) {
     if (two_path(c->g)) {
       c->res = resident_plan(c->g, 4, c->ncu);
       c->res64 = resident_plan(c->g, 8, c->ncu);
+      c->resn = resident_plan_nernst(c->g, c->ncu);
     }
   }
   if ((!c->res.C && !c->res64.C) || c->inbox) return 0;
   long long diag = 0, blocks = 0;
   c->inbox_words = 0;
-  for (const ResidentPlan *p : {&c->res, &c->res64}) {
+  for (const ResidentPlan *p : {&c->res, &c->res64, &c->resn}) {
     if (!p->C) continue;
     c->inbox_words = std::max(c->inbox_words, 2 * p->slot_words);
     diag = std::max(diag, resident_diag_bytes(*p, p == &c->res ? 4 : 8));
@@ -240,7 +241,7 @@ int ensure_resident(socfv_ctx *c) {
     hfree(c->inbox);
     c->inbox = nullptr;
     c->res_diag = nullptr;
-    c->res.C = c->res64.C = 0;           // no room: the other launches need none
+    c->res.C = c->res64.C = c->resn.C = 0;   // no room: the other launches need none
     return 0;
   }
   // words of an earlier buffer at this address could carry a tag of this one
@@ -441,10 +442,8 @@ struct Solver {
   }
 
   // Enqueue k sweeps a.s -> a.s_new as one resident launch (fill: device flag, nullable);
-  // returns the partials' block count.
-  template <typename T>
-  long long launch_resident_sweeps(const SweepArgs<T> &a, int k, bool adj, const int *fill) {
-    const ResidentPlan &rp = res_plan<T>();
+  // returns the partials' block count.  (resident_args: its k tags are taken.)
+  ResidentArgs resident_args(int k) {
     if (c->tag > 0xffffffffu - (unsigned)k) {
       launch_fill_f64((double *)c->inbox, c->inbox_words, 0.0, c->st);
       c->tag = 1;
@@ -456,25 +455,33 @@ struct Solver {
     r.diag = c->res_diag;
     r.abort = &c->dctl->lost;
     r.limit = c->wait_limit;
+    c->tag += (unsigned)k;
+    return r;
+  }
+  template <typename T>
+  long long launch_resident_sweeps(const SweepArgs<T> &a, int k, bool adj, const int *fill) {
+    const ResidentPlan &rp = res_plan<T>();
+    ResidentArgs r = resident_args(k);
     r.fill = fill;
     r.adj = adj;
     launch_resident<T>(a, rp, r, c->st);
-    c->tag += (unsigned)k;
-    return (long long)rp.gx * rp.gy * rp.gz;
+    return rp.blocks();
   }
 
   // The same with the partials reduced on the host; false if the launch was given up (its input
   // is as it was, and this context takes the other launches from then on).
   template <typename T>
   int resident_chunk(const SweepArgs<T> &a, int k, bool adj, double out[NV], bool &ran) {
-    const long long nb = launch_resident_sweeps<T>(a, k, adj, nullptr);
+    return resident_sums(launch_resident_sweeps<T>(a, k, adj, nullptr), res_plan<T>(), out, ran);
+  }
+  int resident_sums(long long nb, ResidentPlan &plan, double out[NV], bool &ran) {
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(&c->hctl->lost, &c->dctl->lost, sizeof(int), hipMemcpyDeviceToHost,
                           c->st));
     TRY(reduce_to_host(c, (int)nb, NV, 0u, out));
     ran = !c->hctl->lost;
     if (!ran) {
-      res_plan<T>().C = 0;
+      plan.C = 0;
       TRY(clear_ctl());
     }
     return 0;
@@ -1406,8 +1413,12 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
     pt.Da = 0.0;
     Solver S{c, &pt};
     TRY(S.setup());
-    HIPCHK(hipMalloc(&eta, sizeof(double) * (size_t)n));
-    launch_fill_f64(eta, n, 0.0, c->st);
+    TRY(ensure_resident(c));
+    TRY(S.clear_ctl());
+    const bool whole = c->resn.C > 0 && c->inbox && !c->tiles_fixed;
+    // the overpotentials; the resident iteration reads one half and writes the other
+    HIPCHK(hipMalloc(&eta, sizeof(double) * (size_t)n * (whole ? 2 : 1)));
+    launch_fill_f64(eta, whole ? 2 * n : n, 0.0, c->st);
     // s_in on pore cells, s_eq = sigma(V - 0) on electrode cells
     launch_init_state(c->g, c->flags, nullptr, p->s_in, p->s_eq, 1, c->s64[0], c->st);
     HIPCHK(hipGetLastError());
@@ -1422,7 +1433,23 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
     double res = INFINITY, out[NV];
     while (S.it < p->max_iter) {
       const long k = std::min<long>(K, p->max_iter - S.it);
-      for (long j = 0; j < k; ++j) {
+      bool ran = false;
+      if (whole && c->resn.C) {
+        SweepArgs<double> w = S.sweep_args<double>(c->s64[cur], c->s64[cur ^ 1], false, c->partial);
+        w.w = faces64(c);
+        double *half[2] = {eta, eta + n};
+        ResidentArgs r = S.resident_args((int)k);
+        r.Da = p->Da; r.K0 = a.K; r.omega = omega; r.V = a.V;
+        r.eta = a.eta;
+        r.eta_new = half[a.eta == eta];
+        launch_resident_nernst(w, c->resn, r, c->st);
+        TRY(S.resident_sums(c->resn.blocks(), c->resn, out, ran));
+        if (ran) {
+          a.eta = r.eta_new;
+          cur ^= 1;
+        }
+      }
+      for (long j = 0; !ran && j < k; ++j) {
         a.s = c->s64[cur];
         a.s_new = c->s64[cur ^ 1];
         a.partial = j == k - 1 ? c->partial : nullptr;
@@ -1430,7 +1457,7 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
         cur ^= 1;
       }
       HIPCHK(hipGetLastError());
-      TRY(reduce_to_host(c, (int)S.nblk, NV, 0u, out));
+      if (!ran) TRY(reduce_to_host(c, (int)S.nblk, NV, 0u, out));
       S.it += k;
       S.it64 += k;
       res = S.res_of(out[0]);
@@ -1449,7 +1476,7 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
       HIPCHK(hipMemcpyAsync(s_out, c->s64[cur], sizeof(double) * (size_t)n,
                             hipMemcpyDeviceToDevice, c->st));
     if (eta_out)
-      HIPCHK(hipMemcpyAsync(eta_out, eta, sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice,
+      HIPCHK(hipMemcpyAsync(eta_out, a.eta, sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice,
                             c->st));
     TRY(leave(c, hip_stream));
     s.iterations = S.it; s.it_fp64 = S.it64; s.status = status; s.residual = res;

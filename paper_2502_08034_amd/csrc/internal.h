@@ -379,11 +379,21 @@ struct ResidentArgs {
   unsigned long long limit;      // longest wait, in ticks of the 100 MHz wall clock
   const int *fill;      // nullable: nonzero = start from zero instead of a.s
   int adj;              // sweeps of the transpose system
+  // the Nernst iteration (a.Da is 0: transport only): reaction number, 1 / sqrt(s_eq (1 - s_eq)),
+  // relaxation, V = logit(s_eq), the overpotentials read and written (they must differ)
+  double Da, K0, omega, V;
+  const double *eta;
+  double *eta_new;
 };
 // a.partial is written (one entry per workgroup); a.s and a.s_new must differ
 template <typename T>
 void launch_resident(const SweepArgs<T> &a, const ResidentPlan &pl, const ResidentArgs &args,
                      hipStream_t st);
+
+// K Nernst iterations in one launch (partials as launch_nernst's)
+ResidentPlan resident_plan_nernst(const Grid &g, int ncu);
+void launch_resident_nernst(const SweepArgs<double> &a, const ResidentPlan &pl,
+                            const ResidentArgs &args, hipStream_t st);
 
 // One problem of a launch over several: its arguments (p without tag0 and K), first workgroup and
 // column length

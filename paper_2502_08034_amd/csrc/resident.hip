@@ -202,8 +202,12 @@ __device__ __forceinline__ Side side_of(int q, int X, int Y) {
   return q < X ? Side{2, q} : Side{3, q - X};
 }
 
+// What a sweep does to a cell beyond s + dt R: nothing; keep held cells of lean columns (whose
+// encoded z faces do not tell them from their neighbours); the Nernst model's electrode update.
+enum { RK_PLAIN = 0, RK_HELD = 1, RK_NERNST = 2 };
+
 // K sweeps of workgroup b of one problem.
-template <typename T, int C, bool HELD>
+template <typename T, int C, int KIND>
 __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const ResidentArgs &p,
                                                const int b) {
   if (a.gate && *a.gate != CTL_RUN) return;
@@ -238,6 +242,7 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
   vec *const lsrc = reinterpret_cast<vec *>(lds + (LEAN ? (copy + 3) / 4 * 4 : 0));
   vec *const ge = reinterpret_cast<vec *>(p.diag) + (long long)b * (C / NV16) * RT;
   unsigned upd = 0, pore = 0;
+  T eta[KIND == RK_NERNST ? C : 1], rate[KIND == RK_NERNST ? C : 1];   // electrode cells
 #pragma unroll
   for (int k0 = 0; k0 < C; k0 += NV16) {
     vec ve, vsrc;
@@ -250,6 +255,12 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
       const T on = in ? T(1) : T(0);
       s[k] = in && !zero ? a.s[i] : T(0);
       if (in && (a.flags[i] & FL_PORE)) pore |= 1u << k;
+      if constexpr (KIND == RK_NERNST) {
+        const int nf = __popc(a.flags[i] & FL_FIBRE);
+        rate[k] = in ? p.Da * (a.kappa ? (T)a.kappa[i] : T(1)) * (T)nf / p.K0 : T(0);
+        eta[k] = in && nf > 0 ? p.eta[i] : T(0);
+        if (in && nf > 0) upd |= 1u << k;
+      }
       q.axm[k] = in ? r.axm : T(0);
       q.axp[k] = in ? r.axp : T(0);
       q.aym[k] = in ? r.aym : T(0);
@@ -359,7 +370,7 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
   auto sweep = [&](auto lastc, int t) {
     constexpr bool LAST = decltype(lastc)::value;
     if constexpr (LEAN) {
-      if (HELD) keep_in_loop(upd);
+      if (KIND == RK_HELD) keep_in_loop(upd);
 #pragma unroll
       for (int k = 0; k <= C; ++k) keep_in_loop(q.tz[k]);
     }
@@ -407,11 +418,24 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
         r = fma(q.ayp[k], yp[v] - c0, r);
         r = fma(azm, dn - c0, r);
         r = fma(azp, up - c0, r);
-        if constexpr (LEAN && HELD)              // held cells keep their value
+        if constexpr (LEAN && KIND == RK_HELD)   // held cells keep their value
           r = (int)(upd << (31 - k)) < 0 ? r : T(0);
-        s[k] = fma(a.dt, r, c0);
+        T next = fma(a.dt, r, c0);
+        if constexpr (KIND == RK_NERNST) {
+          if (upd >> k & 1u) {
+            // the overpotential that balances the transport step, relaxed; the electrode's value
+            const T ei = 2.0 * asinh(-r / (2.0 * rate[k] * sqrt(c0 * (1.0 - c0))));
+            eta[k] = (1.0 - p.omega) * eta[k] + p.omega * ei;
+            next = 1.0 / (1.0 + exp(eta[k] - p.V));
+          }
+        }
+        s[k] = next;
         dn = c0;
-        if (LAST) {
+        if constexpr (LAST && KIND == RK_NERNST) {
+          const double d = pore >> k & 1u ? (next - c0) / a.dt : 0.0;
+          acc[0] += d * d;
+          if (!isfinite(d)) acc[1] += 1.0;
+        } else if (LAST) {
           const double rr = (double)r;
           acc[0] += rr * rr;
           acc[2] += rr;
@@ -511,7 +535,11 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
     const long long o = bx * X + wx + (long long)nx * (by * Y + wy + (long long)ny * z0);
 #pragma unroll
     for (int k = 0; k < C; ++k)
-      if (k < ze) a.s_new[o + pl * k] = s[k];
+      if (k < ze) {
+        a.s_new[o + pl * k] = s[k];
+        if constexpr (KIND == RK_NERNST)
+          if (upd >> k & 1u) p.eta_new[o + pl * k] = eta[k];
+      }
   }
   block_store<NV>(acc, 0u, a.partial + (long long)NV * b);
 }
@@ -520,9 +548,9 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
 #define RESIDENT_KERNEL \
   __global__ void __launch_bounds__(RT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
-template <typename T, int C, bool HELD>
+template <typename T, int C, int KIND>
 RESIDENT_KERNEL k_resident(SweepArgs<T> a, ResidentArgs p) {
-  resident_block<T, C, HELD>(a, p, xcd_tile(blockIdx.x, gridDim.x));
+  resident_block<T, C, KIND>(a, p, xcd_tile(blockIdx.x, gridDim.x));
 }
 
 // Workgroups of several problems in one launch: workgroup g works for problem of[g] of the table.
@@ -539,13 +567,13 @@ RESIDENT_KERNEL k_resident_batch(const ResidentProb<T> *__restrict__ tab,
   const int b = g - e.blk0;
   if constexpr (sizeof(T) == 4) {
     switch (e.C) {
-      case 4: resident_block<T, 4, false>(a, p, b); break;
-      case 8: resident_block<T, 8, false>(a, p, b); break;
-      case 12: resident_block<T, 12, false>(a, p, b); break;
-      case 16: resident_block<T, 16, false>(a, p, b); break;
-      case 20: resident_block<T, 20, false>(a, p, b); break;
-      case 24: resident_block<T, 24, true>(a, p, b); break;
-      default: resident_block<T, 32, true>(a, p, b); break;
+      case 4: resident_block<T, 4, RK_PLAIN>(a, p, b); break;
+      case 8: resident_block<T, 8, RK_PLAIN>(a, p, b); break;
+      case 12: resident_block<T, 12, RK_PLAIN>(a, p, b); break;
+      case 16: resident_block<T, 16, RK_PLAIN>(a, p, b); break;
+      case 20: resident_block<T, 20, RK_PLAIN>(a, p, b); break;
+      case 24: resident_block<T, 24, RK_HELD>(a, p, b); break;
+      default: resident_block<T, 32, RK_HELD>(a, p, b); break;
     }
   }
 }
@@ -604,6 +632,20 @@ ResidentPlan resident_plan(const Grid &g, int bytes, int ncu) {
   return best;
 }
 
+// The Nernst iteration: at most RES_NERNST cells a column (two more numbers each, and the
+// functions' temporaries); an electrode cell costs some ten plain ones, and a column's step is
+// as slow as its wave's slowest, so a cell counts six times the plain sweep's here.
+constexpr int RES_NERNST = 8;
+ResidentPlan resident_plan_nernst(const Grid &g, int ncu) {
+  ResidentPlan best{};
+  resident_splits(g, 8, ncu, [&](ResidentPlan p) {
+    if (p.C > RES_NERNST) return;
+    p.us += 5 * 0.06 * p.C * (((p.X * p.Y + 63) / 64 + 3) / 4);
+    if (!best.C || p.us < best.us) best = p;
+  });
+  return best;
+}
+
 std::vector<ResidentPlan> resident_plans(const Grid &g, int bytes, int ncu) {
   std::vector<ResidentPlan> all, front;
   resident_splits(g, bytes, ncu, [&](const ResidentPlan &p) { all.push_back(p); });
@@ -627,11 +669,25 @@ static void go_resident(const SweepArgs<T> &a, const ResidentPlan &pl, const Res
   const int nb = pl.gx * pl.gy * pl.gz;
   if constexpr (resident_lean(sizeof(T), C)) {
     if (a.pinned) {
-      k_resident<T, C, true><<<nb, RT, bytes, st>>>(a, p);
+      k_resident<T, C, RK_HELD><<<nb, RT, bytes, st>>>(a, p);
       return;
     }
   }
-  k_resident<T, C, false><<<nb, RT, bytes, st>>>(a, p);
+  k_resident<T, C, RK_PLAIN><<<nb, RT, bytes, st>>>(a, p);
+}
+
+void launch_resident_nernst(const SweepArgs<double> &a, const ResidentPlan &pl,
+                            const ResidentArgs &args, hipStream_t st) {
+  ResidentArgs p = args;
+  p.X = pl.X; p.Y = pl.Y; p.gx = pl.gx; p.gy = pl.gy; p.gz = pl.gz;
+  p.block_words = pl.block_words;
+  p.slot_words = pl.slot_words;
+  const int bytes = pl.lds > RESIDENT_LDS_ALONE ? pl.lds : RESIDENT_LDS_ALONE, nb = pl.blocks();
+  switch (pl.C) {
+    case 2: k_resident<double, 2, RK_NERNST><<<nb, RT, bytes, st>>>(a, p); break;
+    case 4: k_resident<double, 4, RK_NERNST><<<nb, RT, bytes, st>>>(a, p); break;
+    default: k_resident<double, 8, RK_NERNST><<<nb, RT, bytes, st>>>(a, p); break;
+  }
 }
 
 template <typename T>

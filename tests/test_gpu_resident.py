@@ -181,3 +181,26 @@ def test_a_batch_whose_launches_are_given_up_still_converges(sv):
         assert st.status == sv.OK and st.residual < 1e-9
         r, _ = sv.solve_soc_steady(pb.ctx, q)
         assert (s - r).abs().max() <= 1e-7          # both within the tolerance of the fixed point
+
+
+@pytest.mark.parametrize("shape,kappa", [((33, 3, 2), False), ((64, 32, 33), True),
+                                         ((129, 63, 65), False), ((150, 80, 81), True)])
+def test_resident_nernst_equals_the_launches(sv, shape, kappa):
+    # the same iteration with the transport rate's terms summed in another order (1e-16 of |s|
+    # <= 1); the overpotential divides it by a k0 sqrt(s (1 - s)) of order one and relaxes
+    inputs = inputs_of(shape, kappa)
+    pb = problem(sv, inputs)
+    p = sv.params(tol=0.0, max_iter=301, check_every=100, s_in=0.2, s_eq=0.7, Da=5.0, mode=0)
+    runs = []
+    for _ in range(2):
+        runs.append(sv.solve_nernst(pb.ctx, p, omega=0.3, want_eta=True))
+        sv.set_tiles(pb.ctx, 0, 0, 0, 1)
+    (s1, e1, r1), (s2, e2, r2) = runs
+    assert r1.iterations == r2.iterations == 301
+    assert (s1 - s2).abs().max() <= 1e-12 and (e1 - e2).abs().max() <= 1e-11
+    assert abs(r1.residual - r2.residual) <= 1e-9 * max(r2.residual, 1e-12)
+    sv.set_tiles(pb.ctx, 0, 0, 0, 1)
+    fresh = problem(sv, inputs)
+    sv.set_wait_limit(fresh.ctx, 0.0)            # given up: the launches go on
+    s3, e3, _ = sv.solve_nernst(fresh.ctx, p, omega=0.3, want_eta=True)
+    assert (s3 - s2).abs().max() <= 1e-12 and (e3 - e2).abs().max() <= 1e-11
