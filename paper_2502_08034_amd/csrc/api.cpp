@@ -2287,7 +2287,16 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     a.pdiv = a.pdu + 6ll * a.nbf;
     a.pfl = a.pdiv + 4ll * a.nbc;
     a.sc = a.pfl + a.nbc;
+    bool whole = flow_cg_whole(a, c->ncu) && p->cg_max < (1 << 20);
+    if (whole) {
+      void *w = nullptr;
+      TRY(alloc(&w, sizeof(unsigned long long) * (size_t)(CGW_WORDS + 1)));
+      a.words = (unsigned long long *)w;
+      a.lost = (int *)(a.words + CGW_WORDS);
+      a.limit = c->wait_limit;
+    }
     TRY(enter(c, hip_stream));
+    if (whole) launch_fill_f64((double *)a.words, CGW_WORDS + 1, 0.0, c->st);
     // start from rest with zero pressure, or resume from the caller's velocity and pressure;
     // zero partials make the first step's CG run to its cap
     if (!p->resume)
@@ -2304,6 +2313,7 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     int m = p->cg_max;
     int guess = 16, from = -1;           // CG iterations to enqueue; where a stalled CG goes on
     double seen = 0.0;
+    unsigned tag = 1;                    // of the whole CG's words
     long group = 1;                      // steps to enqueue
     const long most = n > (1 << 19) ? 1 : 4;   // (a large box's step hides the read)
     int status = SOCFV_NOT_CONVERGED;
@@ -2313,8 +2323,18 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
       // took and some more (a launch past a CG's end returns at once but costs about 2 us); a
       // step that needs more stalls what follows, and the read after the group resumes it.
       for (long s = 0; s < k;) {
-        const long grp = std::min<long>(k - s, group);
-        for (long q = 0; q < grp; ++q) {
+        const long grp = std::min<long>(k - s, whole ? 64 : group);
+        for (long q = 0; whole && q < grp; ++q) {
+          if (tag > 0xffffffffu - (2u * m + 2u)) {
+            launch_fill_f64((double *)a.words, CGW_WORDS, 0.0, c->st);
+            tag = 1;
+          }
+          launch_flow_predict(a, c->st);
+          launch_flow_cg_whole(a, m, tag, c->st);
+          launch_flow_project(a, m, c->st);
+          tag += 2u * m + 2u;
+        }
+        for (long q = 0; !whole && q < grp; ++q) {
           if (q > 0 || from < 0) {
             launch_flow_predict(a, c->st);
             launch_flow_cg_init(a, c->st);
@@ -2328,12 +2348,15 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
         HIPCHK(hipStreamSynchronize(c->st));
         const long ran = (long)c->hres[FS_STEPS] - steps - s;
         s += ran;
-        if (c->hres[FS_STALL] != 0.0) {
+        if (c->hres[FS_STALL] == 2.0) {
+          whole = false;                 // given up: the step again, in separate launches
+          launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
+        } else if (c->hres[FS_STALL] != 0.0) {
           from = (int)c->hres[FS_CG_STEP];
           guess = std::max(8, from / 2);
           group = 1;
           launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
-        } else {
+        } else if (!whole) {
           from = -1;
           const int next = (int)std::ceil(1.2 * (c->hres[FS_CG_TOTAL] - seen) / (double)ran) + 3;
           group = 2 * next < guess ? 1 : std::min(2 * group, most);   // a step of many: alone

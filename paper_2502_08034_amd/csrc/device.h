@@ -193,4 +193,45 @@ __device__ __forceinline__ void resolvew(const SweepArgs<float> &a, const CoefW<
   }
 }
 
+// One value <-> 64-bit words that carry a tag beside 32 bits of it: written and read with relaxed
+// agent-scope atomics, a word with the awaited tag is data and signal in one (see resident.hip).
+template <typename T>
+struct Wire {
+  static constexpr int N = sizeof(T) / 4;     // words per value
+};
+
+__device__ __forceinline__ void put_word(unsigned long long *p, unsigned bits, unsigned tag) {
+  __hip_atomic_store(p, ((unsigned long long)tag << 32) | bits, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ unsigned long long get_word(const unsigned long long *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename T>
+__device__ __forceinline__ void put_value(unsigned long long *p, T v, unsigned tag) {
+  if constexpr (sizeof(T) == 4) {
+    put_word(p, __builtin_bit_cast(unsigned, v), tag);
+  } else {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    put_word(p, (unsigned)b, tag);
+    put_word(p + 1, (unsigned)(b >> 32), tag);
+  }
+}
+
+// Reads a value; false while a word still carries another tag.
+template <typename T>
+__device__ __forceinline__ bool get_value(const unsigned long long *p, unsigned tag, T &v) {
+  if constexpr (sizeof(T) == 4) {
+    const unsigned long long a = get_word(p);
+    v = __builtin_bit_cast(float, (unsigned)a);
+    return (unsigned)(a >> 32) == tag;
+  } else {
+    const unsigned long long a = get_word(p), b = get_word(p + 1);
+    v = __builtin_bit_cast(double, (b << 32) | (unsigned)a);
+    return ((unsigned)(a >> 32) == tag) & ((unsigned)(b >> 32) == tag);
+  }
+}
+
 }  // namespace socfv

@@ -21,7 +21,7 @@
 // faces or cells with coalesced rows.  The CG's scalars are never sent to the host: every
 // block of the next kernel sums the previous kernel's per-block partials itself, in a fixed
 // order, so all blocks take the same (deterministic) values and the same stop decision.
-#include "internal.h"
+#include "device.h"
 
 #include <algorithm>
 #include <vector>
@@ -379,6 +379,256 @@ __global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j) {
   }
 }
 
+// ---- the whole pressure CG of a step in one launch ---------------------------------------
+// For boxes of at most CGW_CELLS cells (one cell per lane, two logical blocks per workgroup, at
+// most one workgroup per CU): r, z, p, d and q stay in registers, and so do the neighbours' d,
+// which a lane advances itself (d = z + beta d from the neighbour's z); what travels between
+// workgroups is z, and the logical blocks' partials, as tagged words that every workgroup sums in
+// the order of the separate kernels.  An iteration then costs its two exchanges instead of two
+// launches and, per step, launches past the end: 100 steps from rest on 48 x 32 x 32 take 8.9 ms
+// against 17 (60 on 64 x 45 x 45 17.7 against 19.1, which is why larger boxes keep the separate
+// kernels), with the same arithmetic cell by cell and sum by sum.  A word is written again only
+// after a sum that its readers have contributed to since they read it, so one slot per word is
+// enough: z and the residual's sums after d.q's, d.q's after the residual's (which therefore
+// have words of their own).  Waits
+// end at a time limit as in the resident sweeps: FS_STALL is then 2, nothing has been written,
+// and the host repeats the step with the separate kernels.
+constexpr int CGW_GROUPS = 2, CGW_LANES = CGW_GROUPS * FB;
+
+// Sum over a group of 256 lanes, as block_total over a block of them.
+__device__ __forceinline__ double group_total(double v, double (*sh)[FB / 64]) {
+  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3, grp = threadIdx.x / FB;
+  v = fwave_sum(v);
+  __syncthreads();
+  if (lane == 0) sh[grp][w] = v;
+  __syncthreads();
+  double t = sh[grp][0];
+#pragma unroll
+  for (int k = 1; k < FB / 64; ++k) t += sh[grp][k];
+  return t;
+}
+
+__global__ void __launch_bounds__(CGW_LANES) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
+  __shared__ double sh[CGW_GROUPS][FB / 64];
+  __shared__ double zl[CGW_LANES], part[3][CGW_GROUPS];
+  __shared__ int slots[CGW_GROUPS];
+  __shared__ int dead;
+  if (a.sc[FS_STALL] != 0.0) return;
+  const Grid g = a.g;
+  const int grp = threadIdx.x / FB, t = threadIdx.x % FB;
+  const int lb = blockIdx.x * CGW_GROUPS + grp;
+  const long long c = (long long)lb * FB + t;
+  const long long sy = g.nx, sz = (long long)g.nx * g.ny;
+  // the place of the logical block's partials (flow_order)
+  const int q8 = a.nbc / 8, r8 = a.nbc % 8, long8 = r8 * (q8 + 1);
+  const int run = lb < long8 ? lb / (q8 + 1) : r8 + (lb - long8) / max(q8, 1);
+  if (t == 0) slots[grp] = 8 * (lb < long8 ? lb % (q8 + 1) : (lb - long8) % max(q8, 1)) + run;
+  const int nb = gridDim.x;
+  if (threadIdx.x == 0) dead = 0;
+  unsigned long long *const zw = a.words, *const pw = a.words + 2 * CGW_CELLS;
+
+  // waits until every word this lane asks for is there
+  auto wait = [&](auto &&all) {
+    unsigned spins = 0;
+    unsigned long long t0 = 0;
+    while (!all()) {
+      if (a.limit == 0 || (++spins & 255u) == 0) {
+        const unsigned long long now = wall_clock64();
+        if (t0 == 0) t0 = now;
+        if (now - t0 >= a.limit ||
+            __hip_atomic_load(a.lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+          dead = 1;
+          __hip_atomic_store(a.lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          break;
+        }
+      }
+    }
+  };
+  // sums of N partials per logical block, the same in every lane (the first group takes them, in
+  // sum_partials' order); the tag says which, and `first` which words
+  auto share = [&](auto &v, unsigned tag, int first) {
+    constexpr int N = sizeof(v) / sizeof(double);
+    if (t == 0)
+#pragma unroll
+      for (int k = 0; k < N; ++k) part[k][grp] = v[k];
+    __syncthreads();
+    // one copy per workgroup: words that all of them polled would be read a hundred times from
+    // the same few lines of memory
+    for (int i = threadIdx.x; i < nb * N * CGW_GROUPS; i += CGW_LANES) {
+      const int to = i / (N * CGW_GROUPS), k = i / CGW_GROUPS % N, from = i % CGW_GROUPS;
+      if (blockIdx.x * CGW_GROUPS + from < a.nbc)
+        put_value<double>(pw + 2 * ((to * CGW_SUMS + first + k) * CGW_BLOCKS + slots[from]),
+                          part[k][from], tag);
+    }
+    const unsigned long long *const mine =
+        pw + 2 * ((blockIdx.x * CGW_SUMS + first) * CGW_BLOCKS);
+    double sum[N] = {};
+    if (grp == 0)
+#pragma unroll 1
+      for (int i = t; i < a.nbc; i += FB) {
+        double x[N];
+        wait([&] {
+          bool ok = true;
+#pragma unroll
+          for (int k = 0; k < N; ++k)
+            ok &= get_value<double>(mine + 2 * (k * CGW_BLOCKS + i), tag, x[k]);
+          return ok;
+        });
+#pragma unroll
+        for (int k = 0; k < N; ++k) sum[k] += x[k];
+      }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      (void)group_total(sum[k], sh);
+      double s = sh[0][0];
+#pragma unroll
+      for (int w = 1; w < FB / 64; ++w) s += sh[0][w];
+      v[k] = s;
+    }
+  };
+
+  // the step's stop target, and k_flow_cg_init's part of this cell
+  double target;
+  {
+    double v = 0.0;
+    for (int k0 = 0; k0 < 3 * a.nbf; k0 += 8 * FB) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = k0 + j * FB + t;
+        const double x = a.pdu[2ll * (k < 3 * a.nbf ? k : 0)];
+        v += k < 3 * a.nbf ? x : 0.0;
+      }
+    }
+    target = a.theta2 * group_total(v, sh) / (a.dt * a.dt);
+  }
+  const unsigned cc = c < g.n ? a.ccode[c] : 0u;
+  const PRow pr = prow_code(cc);
+  double p = 0.0, r = 0.0, z = 0.0;
+  double tot[3] = {0.0, 0.0, 0.0};           // r.z, r.r, the floor's sum
+  if (cc) {
+    const unsigned row = (unsigned)c / (unsigned)g.nx, zz = row / (unsigned)g.ny;
+    const long long ix = c + row;
+    const long long iy = c + (long long)g.nx * zz;
+    const double div = (a.us[0][ix + 1] - a.us[0][ix]) + (a.us[1][iy + g.nx] - a.us[1][iy]) +
+                       (a.us[2][c + sz] - a.us[2][c]);
+    const double b = ((cc & CC_INLET) ? 2.0 * a.p_in : 0.0) - div / a.dt;
+    p = a.p[c];
+    const double ap = pr.diag * p - nb_sum(a.p, c, pr.nb, sy, sz);
+    r = b - ap;
+    z = r / pr.diag;
+    tot[0] += r * z;
+    tot[1] += r * r;
+    const double dp = pr.diag * p;
+    tot[2] += b * b + dp * dp;
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) tot[k] = group_total(tot[k], sh);
+  // neighbours: those of this workgroup's cells come from its LDS copy of z, the others as words
+  const int off[6] = {-1, 1, -(int)sy, (int)sy, -(int)sz, (int)sz};
+  unsigned far = 0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const int at = (int)threadIdx.x + off[k];
+    if ((pr.nb >> k & 1u) && (at < 0 || at >= CGW_LANES)) far |= 1u << k;
+  }
+  double dn[6], d = 0.0, rz_old = 0.0, floor2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) dn[k] = 0.0;
+  int j = 0;
+  bool done = false;
+  for (;; ++j) {
+    const unsigned tag = tag0 + 2u * (unsigned)j;
+    // the cells' z and the sums of the residual
+    if (cc) put_value<double>(zw + 2 * c, z, tag);
+    zl[threadIdx.x] = z;
+    if (j == 0) {
+      share(tot, tag, 0);
+      floor2 = (CG_FLOOR * 2.220446049250313e-16) * (CG_FLOOR * 2.220446049250313e-16) * tot[2];
+    } else {
+      double two[2] = {tot[0], tot[1]};
+      share(two, tag, 0);
+      tot[0] = two[0];
+      tot[1] = two[1];
+    }
+    if (dead) break;
+    if (j >= m) break;
+    if (tot[1] <= fmax(target, floor2)) {
+      done = true;
+      break;
+    }
+    // d = z + beta d, q = A d (k_flow_cg_a)
+    const double beta = j == 0 ? 0.0 : tot[0] / rz_old;
+    double zn[6];
+    if (far)
+      wait([&] {
+        // both z neighbours' words in flight at once (a near one reads this cell's); x and y
+        // neighbours are far only at the ends of the workgroup's run of cells
+        bool ok = true;
+#pragma unroll
+        for (int k = 4; k < 6; ++k)
+          ok &= get_value<double>(zw + 2 * (c + ((far >> k & 1u) ? off[k] : 0)), tag, zn[k]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (far >> k & 1u) ok &= get_value<double>(zw + 2 * (c + off[k]), tag, zn[k]);
+        return ok;
+      });
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+      if (!(far >> k & 1u)) zn[k] = zl[(pr.nb >> k & 1u) ? threadIdx.x + off[k] : threadIdx.x];
+    double qv = 0.0;
+    double dq[1] = {0.0};
+    if (cc) {
+      auto sum = [&](const double (&v)[6]) {
+        return (((pr.nb & 1u) ? v[0] : 0.0) + ((pr.nb & 2u) ? v[1] : 0.0)) +
+               (((pr.nb & 4u) ? v[2] : 0.0) + ((pr.nb & 8u) ? v[3] : 0.0)) +
+               (((pr.nb & 16u) ? v[4] : 0.0) + ((pr.nb & 32u) ? v[5] : 0.0));
+      };
+      double nbs;
+      if (j == 0) {
+        d = z;
+        nbs = sum(zn);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) dn[k] = zn[k];
+      } else {
+        d = fma(beta, d, z);
+        nbs = fma(beta, sum(dn), sum(zn));
+#pragma unroll
+        for (int k = 0; k < 6; ++k) dn[k] = fma(beta, dn[k], zn[k]);
+      }
+      qv = fma(pr.diag, d, -nbs);
+      dq[0] += d * qv;
+    }
+    dq[0] = group_total(dq[0], sh);
+    share(dq, tag + 1u, 3);
+    if (dead) break;
+    // the update (k_flow_cg_b)
+    const double alpha = tot[0] / dq[0];
+    rz_old = tot[0];
+    double rzn = 0.0, rrn = 0.0;
+    if (cc) {
+      p = fma(alpha, d, p);
+      r = fma(-alpha, qv, r);
+      z = r / pr.diag;
+      rzn += r * z;
+      rrn += r * r;
+    }
+    tot[0] = group_total(rzn, sh);
+    tot[1] = group_total(rrn, sh);
+  }
+  __syncthreads();
+  if (dead) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[FS_STALL] = 2.0;
+    return;
+  }
+  (void)done;
+  if (cc) a.p[c] = p;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    a.sc[FS_CG_STEP] = (double)j;
+    a.sc[FS_DONE] = 1.0;
+  }
+}
+
 // ---- projection: u' = u* - dt (G p + gbc); partials [sum (u' - u)^2, sum u'^2] -----------
 // A step whose CG has neither met its target nor reached the cap has run out of launched
 // iterations: nothing is projected, and the launches behind this one return until the host has
@@ -526,6 +776,12 @@ void launch_flow_cg_init(const FlowArgs &a, hipStream_t st) {
 void launch_flow_cg_iter(const FlowArgs &a, int j, hipStream_t st) {
   k_flow_cg_a<<<a.nbc, FB, 0, st>>>(a, j);
   k_flow_cg_b<<<a.nbc, FB, 0, st>>>(a, j);
+}
+bool flow_cg_whole(const FlowArgs &a, int ncu) {
+  return a.g.n <= CGW_CELLS && (a.nbc + CGW_GROUPS - 1) / CGW_GROUPS <= ncu;
+}
+void launch_flow_cg_whole(const FlowArgs &a, int m, unsigned tag0, hipStream_t st) {
+  k_flow_cg_whole<<<(a.nbc + CGW_GROUPS - 1) / CGW_GROUPS, CGW_LANES, 0, st>>>(a, m, tag0);
 }
 void launch_flow_project(const FlowArgs &a, int cap, hipStream_t st) {
   k_flow_project<<<dim3(a.nbf, 3), FB, 0, st>>>(a, cap);

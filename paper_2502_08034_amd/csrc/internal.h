@@ -211,6 +211,9 @@ struct FlowArgs {
   double dt, p_in, theta2;        // theta2: (CG stop factor)^2
   int nbc, nbf;          // blocks of the cell kernels / per face array of the face kernels
   int *corder, *forder[3];        // logical block of each workgroup (flow_order)
+  unsigned long long *words;      // exchange words of the whole CG (CGW_WORDS)
+  int *lost;                      // raised when a wait of the whole CG ran into its limit
+  unsigned long long limit;       // that limit, in ticks of the 100 MHz clock
   double *prz[2], *prr[2], *pdq;  // per-block CG partials (cell kernels), ping-pong by parity
   double *pdu;           // per-block [sum du^2, sum u^2] of the projection, (3 nbf) x 2
   double *pdiv;          // per-block [max |div u|, inlet flux] (cell kernels), nbc x 2
@@ -226,6 +229,13 @@ void launch_flow_predict(const FlowArgs &a, hipStream_t st);
 void launch_flow_cg_init(const FlowArgs &a, hipStream_t st);
 void launch_flow_cg_iter(const FlowArgs &a, int j, hipStream_t st);   // both CG kernels
 // cap: CG iterations after which a step goes on without having met its target
+// a step's CG (cg_init included) in one launch of up to m iterations; 2 m + 2 tags from tag0
+constexpr long long CGW_CELLS = 1ll << 17;       // largest box
+constexpr int CGW_BLOCKS = 512;                  // its logical blocks
+constexpr int CGW_SUMS = 4;                      // r.z, r.r, the floor's, d.q
+constexpr long long CGW_WORDS = 2 * CGW_CELLS + 2ll * CGW_SUMS * CGW_BLOCKS * (CGW_BLOCKS / 2);
+bool flow_cg_whole(const FlowArgs &a, int ncu);
+void launch_flow_cg_whole(const FlowArgs &a, int m, unsigned tag0, hipStream_t st);
 void launch_flow_project(const FlowArgs &a, int cap, hipStream_t st);
 void launch_flow_check(const FlowArgs &a, hipStream_t st);   // fills pdiv
 

@@ -169,3 +169,22 @@ def test_cg_cap_and_stalled_steps(sv):
         assert cap > 17 or st.cg_iterations == 11 * cap
     st = sv.solve_stokes(ctx, cfl=2.0, max_steps=9, cg_theta=1e30, cg_max=40, tol=0.0)[4]
     assert st.steps == 9 and st.cg_iterations <= 40
+
+
+@pytest.mark.parametrize("shape", [(16, 12, 12), (48, 32, 32), (67, 41, 29), (96, 50, 54)])
+def test_cg_in_one_launch_equals_the_separate_kernels(sv, shape):
+    # the same sums in the same order: flows equal bit for bit (wait limit 0: every single-launch
+    # CG of more than one workgroup is given up and its step repeated by the separate kernels)
+    g = I.fibres_nonoverlap(*shape, 2.5, 0.88, 11)
+    solid = torch.as_tensor(g.solid, device="cuda")
+    runs = []
+    for limit in (1.0, 0.0):
+        ctx = sv.setup_geometry(solid)
+        sv.set_wait_limit(ctx, limit)
+        for kw in (dict(cg_max=256), dict(cg_max=5)):
+            runs.append(sv.solve_stokes(ctx, cfl=3.0, max_steps=60, tol=0.0, want_pressure=True,
+                                        **kw))
+    for a, b in zip(runs[:2], runs[2:]):
+        assert a[4].steps == b[4].steps == 60 and a[4].cg_iterations == b[4].cg_iterations
+        for x, y in zip(a[:4], b[:4]):
+            assert torch.equal(x, y)
