@@ -776,16 +776,109 @@ struct Solver {
   }
 };
 
+// Device buffers of a batch's resident launches.
+struct BatchResident {
+  ResidentProb<float> *tab = nullptr;    // two tables, by the corrections' parity
+  ResidentProb<double> *tab64 = nullptr;
+  int *of = nullptr;
+  unsigned long long *inbox = nullptr;
+  char *diag = nullptr;
+  double *part = nullptr;
+  BatchR64 *refresh = nullptr;           // two tables
+  int *refresh_of = nullptr;
+  long long words = 0;
+  unsigned tag = 1;
+  bool ready = false;
+
+  // false: no room
+  bool make(int n, int ncu, long long refresh_items, hipStream_t st) {
+    words = 2 * RESIDENT_BLOCK_WORDS * ncu;
+    ready = hipMalloc(&tab, sizeof(*tab) * 2 * n) == hipSuccess &&
+            hipMalloc(&tab64, sizeof(*tab64) * n) == hipSuccess &&
+            hipMalloc(&of, sizeof(int) * ncu) == hipSuccess &&
+            hipMalloc(&inbox, sizeof(*inbox) * words) == hipSuccess &&
+            hipMalloc(&diag, (size_t)RESIDENT_BLOCK_DIAG * ncu) == hipSuccess &&
+            hipMalloc(&part, sizeof(double) * NV * ncu) == hipSuccess &&
+            hipMalloc(&refresh, sizeof(*refresh) * 2 * n) == hipSuccess &&
+            hipMalloc(&refresh_of, sizeof(int) * refresh_items) == hipSuccess;
+    if (ready) launch_fill_f64((double *)inbox, words, 0.0, st);
+    else (void)hipGetLastError();
+    return ready;
+  }
+  // the first of k tags
+  unsigned take(int k, hipStream_t st) {
+    if (tag > 0xffffffffu - (unsigned)k) {
+      launch_fill_f64((double *)inbox, words, 0.0, st);
+      tag = 1;
+    }
+    const unsigned t = tag;
+    tag += (unsigned)k;
+    return t;
+  }
+  // the arguments of a problem whose workgroups start at blk
+  ResidentArgs args(const ResidentPlan &pl, int blk, int ncu) const {
+    ResidentArgs p{};
+    p.X = pl.X; p.Y = pl.Y; p.gx = pl.gx; p.gy = pl.gy; p.gz = pl.gz;
+    p.inbox = inbox + RESIDENT_BLOCK_WORDS * blk;
+    p.block_words = RESIDENT_BLOCK_WORDS;
+    p.slot_words = RESIDENT_BLOCK_WORDS * ncu;
+    p.diag = diag + RESIDENT_BLOCK_DIAG * blk;
+    return p;
+  }
+  void release() {
+    hfree(tab); hfree(tab64); hfree(of); hfree(inbox); hfree(diag); hfree(part);
+    hfree(refresh); hfree(refresh_of);
+  }
+};
+
+// The problems of the next launch (in the order given, the first always among them) and their
+// splits: for every time per sweep that some split takes, the problems that fit the chip at their
+// fewest workgroups within that time; of these the choice that sweeps the most cells per time.
+void choose_resident(const std::vector<int> &order, const std::vector<std::vector<ResidentPlan>> &plans,
+                     socfv_ctx *const *ctxs, int ncu, std::vector<int> &set,
+                     std::vector<const ResidentPlan *> &pick) {
+  std::vector<double> times;
+  for (int i : order)
+    for (const ResidentPlan &p : plans[i]) times.push_back(p.us - p.words_us);
+  std::sort(times.begin(), times.end());
+  double best = 0;
+  for (size_t t = 0; t < times.size(); ++t) {
+    if (t > 0 && times[t] < times[t - 1] + 0.02) continue;
+    std::vector<int> who;
+    std::vector<const ResidentPlan *> with;
+    int used = 0;
+    double cells = 0, us = 0, words = 0;
+    for (int i : order)
+      for (const ResidentPlan &p : plans[i]) {       // fewest workgroups first
+        if (p.us - p.words_us > times[t] + 0.02) continue;
+        if (used + p.blocks() > ncu) break;
+        who.push_back(i);
+        with.push_back(&p);
+        used += p.blocks();
+        cells += (double)ctxs[i]->g.n;
+        us = std::max(us, p.us - p.words_us);
+        words += p.words_us;
+        break;
+      }
+    if (who.empty() || who[0] != order[0]) continue;
+    const double rate = cells / (us + words);
+    if (rate > best) {
+      best = rate;
+      set = who;
+      pick = with;
+    }
+  }
+}
+
 // The resident part of a batched solve: every problem that fits the chip, several at a time, one
 // launch per chunk of K sweeps.  Which problems share a launch, and how many workgroups each gets,
-// is chosen anew after every read of the states: those with the most sweeps left first (from the
-// residual's decay), as many as fit at their fewest workgroups, then more workgroups to whichever
-// is slowest while any are left, so that a launch's problems end together.  On return h_ctl holds
+// is chosen anew after every read of the states (choose_resident), those with the most sweeps left
+// first (from the residual's decay).  On return h_ctl holds
 // every problem's state: CTL_RUN for one that does not fit, CTL_LOST for one whose launch was
 // given up; a problem's correction is in s32[0].
 int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver *S, int K,
                    SolveCtl *d_ctl, SolveCtl *h_ctl, BatchProb *d_probs, double *d_out,
-                   hipStream_t bs) {
+                   BatchResident &br, hipStream_t bs) {
   const int ncu = ctxs[0]->ncu;
   std::vector<std::vector<ResidentPlan>> plans(n);
   bool any = false;
@@ -795,30 +888,18 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
       any = any || !plans[i].empty();
     }
   if (!any) return 0;
-  ResidentProb<float> *d_tab = nullptr;
-  int *d_of = nullptr;
-  unsigned long long *d_inbox = nullptr;
-  char *d_diag = nullptr;
-  double *d_part = nullptr;
-  const long long words = 2 * RESIDENT_BLOCK_WORDS * ncu;
-  const int rc = [&]() -> int {
-    if (hipMalloc(&d_tab, sizeof(ResidentProb<float>) * 2 * n) != hipSuccess ||
-        hipMalloc(&d_of, sizeof(int) * ncu) != hipSuccess ||
-        hipMalloc(&d_inbox, sizeof(unsigned long long) * words) != hipSuccess ||
-        hipMalloc(&d_diag, (size_t)RESIDENT_BLOCK_DIAG * ncu) != hipSuccess ||
-        hipMalloc(&d_part, sizeof(double) * NV * ncu) != hipSuccess) {
-      (void)hipGetLastError();
-      return 0;                          // no room: the tiled launches need less
-    }
-    launch_fill_f64((double *)d_inbox, words, 0.0, bs);
+  {
+    long long items = 0;
+    for (int i = 0; i < n; ++i) items += march64_blocks(ctxs[i]->g);
+    if (!br.make(n, ncu, items, bs)) return 0;       // no room: the tiled launches need less
     HIPCHK(hipGetLastError());
-    unsigned tag = 1;
     std::vector<double> sweeps_left(n, 1e18);    // estimated
     std::vector<long long> it_seen(n, 0);
     std::vector<double> ri_seen(n, 0.0);
     std::vector<ResidentProb<float>> tab(2 * n);
     std::vector<BatchProb> hp;
-    std::vector<int> of(ncu);
+    std::vector<BatchR64> ref(2 * n);
+    std::vector<int> of(ncu), ref_of;
     for (;;) {
       // the problems of the next launches, and their splits
       std::vector<int> order, set;
@@ -827,30 +908,16 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
       if (order.empty()) break;
       std::stable_sort(order.begin(), order.end(),
                        [&](int a, int b) { return sweeps_left[a] > sweeps_left[b]; });
-      std::vector<size_t> pick(n, 0);
-      int used = 0;
-      for (int i : order)
-        if (used + plans[i][0].blocks() <= ncu) {
-          set.push_back(i);
-          used += plans[i][0].blocks();
-        }
-      for (;;) {
-        int slow = -1;
-        for (int i : set)
-          if (slow < 0 || plans[i][pick[i]].us > plans[slow][pick[slow]].us) slow = i;
-        if (pick[slow] + 1 >= plans[slow].size()) break;
-        const int more = plans[slow][pick[slow] + 1].blocks() - plans[slow][pick[slow]].blocks();
-        if (used + more > ncu) break;
-        ++pick[slow];
-        used += more;
-      }
+      std::vector<const ResidentPlan *> pick;
+      choose_resident(order, plans, ctxs, ncu, set, pick);
       hp.assign(n, BatchProb{});
       for (int i = 0; i < n; ++i) hp[i].ctl = d_ctl + i;
       int blk = 0, lds = 0;
+      ref_of.clear();
       for (size_t k = 0; k < set.size(); ++k) {
         const int i = set[k];
         socfv_ctx *c = ctxs[i];
-        const ResidentPlan &pl = plans[i][pick[i]];
+        const ResidentPlan &pl = *pick[k];
         BatchProb &b = hp[i];
         b.gx = pl.gx; b.gy = pl.gy; b.gz = pl.gz;
         b.tile0 = blk;
@@ -860,26 +927,42 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
           ResidentProb<float> &e = tab[par * n + k];
           e = ResidentProb<float>{};
           e.a = S[i].sweep_args<float>(c->s32[par], c->s32[par ^ 1], true,
-                                       d_part + (long long)NV * blk);
+                                       br.part + (long long)NV * blk);
           e.a.w = faces32(c);
           e.a.gate = &d_ctl[i].state;
-          e.p.X = pl.X; e.p.Y = pl.Y; e.p.gx = pl.gx; e.p.gy = pl.gy; e.p.gz = pl.gz;
-          e.p.inbox = d_inbox + RESIDENT_BLOCK_WORDS * blk;
-          e.p.block_words = RESIDENT_BLOCK_WORDS;
-          e.p.slot_words = RESIDENT_BLOCK_WORDS * ncu;
-          e.p.diag = d_diag + RESIDENT_BLOCK_DIAG * blk;
+          e.p = br.args(pl, blk, ncu);
           e.p.abort = &d_ctl[i].lost;
           e.p.limit = c->wait_limit;
           e.p.fill = &d_ctl[i].fill;
           e.blk0 = blk;
           e.C = pl.C;
+          // the refresh after this chunk takes the correction that the chunk wrote
+          BatchR64 &q = ref[par * n + k];
+          q = BatchR64{};
+          q.a.g = c->g; q.a.flags = c->flags; q.a.w = faces64(c); q.a.kappa = c->kappa;
+          q.a.delta = c->s32[par ^ 1]; q.a.r0 = c->r0;
+          q.a.s_in = p[i].s_in; q.a.s_eq = p[i].s_eq; q.a.Da = p[i].Da;
+          q.a.pinned = S[i].pinned; q.a.lo = S[i].lo; q.a.hi = S[i].hi;
+          q.a.partial = c->partial;
+          q.a.gate = &d_ctl[i].state;
+          q.a.gate_val = CTL_REFRESH;
+          q.a.sel = &d_ctl[i].cur;
+          q.a.pair[0] = c->s64[0];
+          q.a.pair[1] = c->s64[1];
+          march64_shape(c->g, q.gx, q.gy, q.gz, q.a.zc);
+          q.blk0 = (int)ref_of.size();
         }
+        ref_of.insert(ref_of.end(), march64_blocks(c->g), (int)k);
         for (int t = 0; t < pl.blocks(); ++t) of[blk++] = (int)k;
         lds = std::max(lds, pl.lds);
       }
-      HIPCHK(hipMemcpyAsync(d_tab, tab.data(), sizeof(ResidentProb<float>) * 2 * n,
+      HIPCHK(hipMemcpyAsync(br.tab, tab.data(), sizeof(ResidentProb<float>) * 2 * n,
                             hipMemcpyHostToDevice, bs));
-      HIPCHK(hipMemcpyAsync(d_of, of.data(), sizeof(int) * blk, hipMemcpyHostToDevice, bs));
+      HIPCHK(hipMemcpyAsync(br.of, of.data(), sizeof(int) * blk, hipMemcpyHostToDevice, bs));
+      HIPCHK(hipMemcpyAsync(br.refresh, ref.data(), sizeof(BatchR64) * 2 * n,
+                            hipMemcpyHostToDevice, bs));
+      HIPCHK(hipMemcpyAsync(br.refresh_of, ref_of.data(), sizeof(int) * ref_of.size(),
+                            hipMemcpyHostToDevice, bs));
       HIPCHK(hipMemcpyAsync(d_probs, hp.data(), sizeof(BatchProb) * n, hipMemcpyHostToDevice, bs));
       // chunks until the next read: up to four, not far beyond the first problem's end (its
       // workgroups would idle)
@@ -887,24 +970,12 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
       for (int i : set) least = std::min(least, sweeps_left[i]);
       const int rounds = least > 1e17 ? 2 : (int)std::max(1.0, std::min(4.0, std::ceil(least / K)));
       for (int r = 0; r < rounds; ++r) {
-        if (tag > 0xffffffffu - (unsigned)K) {
-          launch_fill_f64((double *)d_inbox, words, 0.0, bs);
-          tag = 1;
-        }
-        launch_resident_batch<float>(d_tab + (r & 1) * n, d_of, blk, lds, tag, K, bs);
-        tag += (unsigned)K;
-        launch_batch_reduce(d_probs, n, d_part, d_out, bs);
+        launch_resident_batch<float>(br.tab + (r & 1) * n, br.of, blk, lds, br.take(K, bs), K, bs);
+        launch_batch_reduce(d_probs, n, br.part, d_out, bs);
         launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_CHUNK, d_out, K, bs);
-        for (int i : set) {
-          socfv_ctx *c = ctxs[i];
-          RefreshArgs a;
-          a.g = c->g; a.flags = c->flags; a.w = faces64(c); a.kappa = c->kappa;
-          a.s64 = nullptr; a.delta = c->s32[1]; a.s64_new = nullptr; a.r0 = c->r0;
-          a.s_in = p[i].s_in; a.s_eq = p[i].s_eq; a.Da = p[i].Da; a.pinned = S[i].pinned;
-          a.lo = S[i].lo; a.hi = S[i].hi; a.partial = c->partial; a.zc = S[i].t.zc;
-          launch_refresh_gated(a, c->s64[0], c->s64[1], d_ctl + i, bs);
-          std::swap(c->s32[0], c->s32[1]);       // the chunk's output is the next one's input
-        }
+        launch_batch_refresh(br.refresh + (r & 1) * n, br.refresh_of, (int)ref_of.size(), bs);
+        // the chunk's output is the next one's input
+        for (int i : set) std::swap(ctxs[i]->s32[0], ctxs[i]->s32[1]);
         launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_REFRESH, nullptr, 0, bs);
       }
       HIPCHK(hipGetLastError());
@@ -927,10 +998,7 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
       }
     }
     return 0;
-  }();
-  (void)hipStreamSynchronize(bs);
-  hfree(d_tab); hfree(d_of); hfree(d_inbox); hfree(d_diag); hfree(d_part);
-  return rc;
+  }
 }
 
 // outputs of state s: per-block partials at `partial` (outputs_blocks x NV2 doubles), the
@@ -1723,6 +1791,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
   int *d_mitem = nullptr;
   double *d_mpart = nullptr;
   SolveCtl *d_ctl = nullptr, *h_ctl = nullptr;
+  BatchResident br;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   auto cleanup = [&]() {
@@ -1730,6 +1799,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
     if (graph) (void)hipGraphDestroy(graph);
     (void)hipStreamSynchronize(bs);
     hfree(d_probs); hfree(d_tiles); hfree(d_work); hfree(d_nwork); hfree(d_grab);
+    br.release();
     hfree(d_part); hfree(d_out); hfree(d_ctl); hfree(d_m); hfree(d_mitem); hfree(d_mpart);
     if (h_work) (void)hipHostFree(h_work);
     if (h_out) (void)hipHostFree(h_out);
@@ -1793,7 +1863,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
     }
     HIPCHK(hipMemcpyAsync(d_ctl, h_ctl, sizeof(SolveCtl) * n, hipMemcpyHostToDevice, bs));
     HIPCHK(hipStreamSynchronize(bs));
-    TRY(batch_resident(n, ctxs, p, S.data(), K, d_ctl, h_ctl, d_probs, d_out, bs));
+    TRY(batch_resident(n, ctxs, p, S.data(), K, d_ctl, h_ctl, d_probs, d_out, br, bs));
     // what is left for the tiled launches: problems that do not fit the chip, and those whose
     // resident launch was given up (their corrections go into the state first)
     bool left = false;
@@ -2107,6 +2177,82 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       kmax = std::max(kmax, nk[i]);
       if (nk[i]) items_max += march64_blocks(ctxs[i]->g);
     }
+    // Problems that fit the chip in FP64 polish in resident launches, several at a time.
+    std::vector<char> polished(n, 0);
+    if (kmax > 0 && br.ready) {
+      const int ncu = ctxs[0]->ncu;
+      std::vector<std::vector<ResidentPlan>> plans(n);
+      std::vector<int> order;
+      for (int i = 0; i < n; ++i)
+        if (nk[i] > 0 && two_path(ctxs[i]->g) && !ctxs[i]->tiles_fixed) {
+          plans[i] = resident_plans(ctxs[i]->g, 8, ncu);
+          if (!plans[i].empty()) order.push_back(i);
+        }
+      HIPCHK(hipEventRecord(ctxs[0]->t0, bs));
+      while (!order.empty()) {
+        std::vector<int> set, of(ncu);
+        std::vector<const ResidentPlan *> pick;
+        choose_resident(order, plans, ctxs, ncu, set, pick);
+        std::vector<ResidentProb<double>> tab(n);
+        std::vector<BatchProb> hp(n, BatchProb{});
+        int blk = 0, lds = 0, most = 0;
+        for (size_t k = 0; k < set.size(); ++k) {
+          const int i = set[k];
+          const ResidentPlan &pl = *pick[k];
+          ResidentProb<double> &e = tab[k];
+          e.a = S[i].sweep_args<double>(ctxs[i]->s64[cur[i]], ctxs[i]->s64[cur[i] ^ 1], false,
+                                        br.part + (long long)NV * blk);
+          e.a.w = faces64(ctxs[i]);
+          e.p = br.args(pl, blk, ncu);
+          e.p.K = (int)nk[i];
+          e.p.abort = &d_ctl[i].lost;
+          e.p.limit = ctxs[i]->wait_limit;
+          e.blk0 = blk;
+          e.C = pl.C;
+          hp[i].gx = pl.gx; hp[i].gy = pl.gy; hp[i].gz = pl.gz;
+          hp[i].tile0 = blk;
+          for (int t = 0; t < pl.blocks(); ++t) of[blk++] = (int)k;
+          lds = std::max(lds, pl.lds);
+          most = std::max(most, (int)nk[i]);
+        }
+        HIPCHK(hipMemcpyAsync(br.tab64, tab.data(), sizeof(ResidentProb<double>) * n,
+                              hipMemcpyHostToDevice, bs));
+        HIPCHK(hipMemcpyAsync(br.of, of.data(), sizeof(int) * blk, hipMemcpyHostToDevice, bs));
+        HIPCHK(hipMemcpyAsync(d_probs, hp.data(), sizeof(BatchProb) * n, hipMemcpyHostToDevice,
+                              bs));
+        for (int i : set) h_ctl[i].lost = 0;
+        HIPCHK(hipMemcpyAsync(d_ctl, h_ctl, sizeof(SolveCtl) * n, hipMemcpyHostToDevice, bs));
+        launch_resident_batch<double>(br.tab64, br.of, blk, lds, br.take(most, bs), 0, bs);
+        launch_batch_reduce(d_probs, n, br.part, d_out, bs);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(h_out, d_out, sizeof(double) * NV * n, hipMemcpyDeviceToHost, bs));
+        HIPCHK(hipMemcpyAsync(h_ctl, d_ctl, sizeof(SolveCtl) * n, hipMemcpyDeviceToHost, bs));
+        HIPCHK(hipStreamSynchronize(bs));
+        for (int i : set) {
+          order.erase(std::find(order.begin(), order.end(), i));
+          if (h_ctl[i].lost) continue;           // given up: the march polishes it below
+          polished[i] = 1;
+          cur[i] ^= 1;
+          res[i] = S[i].res_of(h_out[(size_t)NV * i]);
+          TRY(S[i].check(h_out + (size_t)NV * i, res[i]));
+        }
+      }
+      HIPCHK(hipEventRecord(ctxs[0]->t1, bs));
+      HIPCHK(hipEventSynchronize(ctxs[0]->t1));
+      float ms = 0;
+      HIPCHK(hipEventElapsedTime(&ms, ctxs[0]->t0, ctxs[0]->t1));
+      kmax = 0;
+      for (int i = 0; i < n; ++i) {
+        if (polished[i]) {
+          S[i].it += nk[i];
+          S[i].it64 += nk[i];
+          S[i].sw64 += nk[i];
+          S[i].ms64 += ms;               // shared by every problem in it
+        } else {
+          kmax = std::max(kmax, nk[i]);
+        }
+      }
+    }
     if (kmax > 0) {
       HIPCHK(hipMalloc(&d_m, sizeof(BatchM64) * n));
       HIPCHK(hipMalloc(&d_mitem, sizeof(int) * items_max));
@@ -2118,7 +2264,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
         hm.clear();
         hitem.clear();
         for (int i = 0; i < n; ++i) {
-          if (nk[i] <= j) continue;
+          if (nk[i] <= j || polished[i]) continue;
           socfv_ctx *c = ctxs[i];
           BatchM64 b{};
           b.a = S[i].sweep_args<double>(nullptr, nullptr, false, nullptr);
@@ -2144,7 +2290,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       TRY(build_m(0));
       std::vector<char> ends(kmax, 0);
       for (int i = 0; i < n; ++i)
-        if (nk[i]) ends[nk[i] - 1] = 1;
+        if (nk[i] && !polished[i]) ends[nk[i] - 1] = 1;
       HIPCHK(hipEventRecord(ctxs[0]->t0, bs));
       for (long j = 0; j < kmax; ++j) {
         if (j > 0 && ends[j - 1]) TRY(build_m(j));
@@ -2158,7 +2304,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       float ms = 0;
       HIPCHK(hipEventElapsedTime(&ms, ctxs[0]->t0, ctxs[0]->t1));
       for (int i = 0; i < n; ++i) {
-        if (!nk[i]) continue;
+        if (!nk[i] || polished[i]) continue;
         const double *out = h_out + (size_t)NV * i;
         S[i].it += nk[i];
         S[i].it64 += nk[i];

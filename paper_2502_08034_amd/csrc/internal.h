@@ -251,6 +251,35 @@ dim3 sweep2_grid(const Grid &g, const Tiles &t);
 // adj: sweeps of the transpose system (correction form only)
 void launch_sweep2(const SweepArgs<float> &a, const Tiles &t, hipStream_t st, bool adj = false);
 
+// Arguments of every FP64 march kernel (the fields an operation does not use are unset).
+struct March64Args {
+  Grid g;
+  const uint8_t *flags;
+  Faces<double> w;
+  const float *kappa;
+  const double *s;      // state (refresh: base state s64)
+  const float *delta;   // refresh: FP32 correction added to s (nullable)
+  double *s_new;        // sweep: s + dt R; refresh: s + delta (held cells s_eq)
+  float *r0;            // refresh: R(s + delta) in FP32
+  double dt, s_in, s_eq, Da;
+  int pinned;
+  double lo, hi;        // bound check on the written state
+  double *partial;      // per block: sweep / refresh NV values, outputs NV2 values
+  int zc;
+  const int *gate;      // nullable: run only if *gate == gate_val
+  int gate_val;
+  const int *sel;       // nullable: s = pair[*sel], s_new = pair[*sel ^ 1]
+  double *pair[2];
+};
+
+// One problem's gated refresh in a launch over several: its march grid and first item
+struct BatchR64 {
+  March64Args a;
+  int gx, gy, gz, blk0;
+};
+// the (gated) refreshes of several problems in one launch over nitems items, item i problem of[i]'s
+void launch_batch_refresh(const BatchR64 *probs, const int *of, int nitems, hipStream_t st);
+
 // ---- kernels (launch wrappers; all enqueue on `st`) ---------------------------------
 
 void launch_flags(const Grid &g, const uint8_t *solid, uint8_t *flags, double *partial,
@@ -366,15 +395,16 @@ struct ResidentPlan {
   int gx, gy, gz;       // sub-boxes along x, y, z
   int lds;              // bytes of LDS per workgroup
   long long block_words, slot_words;   // exchange words per workgroup, and per slot
-  double us;            // modelled time per sweep
+  double us;            // modelled time per sweep, of which for exchanged words:
+  double words_us;
   int blocks() const { return gx * gy * gz; }
 };
 // The fastest split of a box over at most ncu workgroups (C = 0: it does not fit), and the splits
 // that are faster than every one with fewer workgroups; bytes: of a value (4 or 8)
 ResidentPlan resident_plan(const Grid &g, int bytes, int ncu);
 std::vector<ResidentPlan> resident_plans(const Grid &g, int bytes, int ncu);
-// Most exchange words and bytes of diagonals of any FP32 workgroup
-constexpr long long RESIDENT_BLOCK_WORDS = 8ll * RESIDENT_LANES;
+// Most exchange words and bytes of diagonals of any workgroup, FP32 or FP64
+constexpr long long RESIDENT_BLOCK_WORDS = 10ll * RESIDENT_LANES;
 constexpr long long RESIDENT_BLOCK_DIAG = 32ll * RESIDENT_LANES * 4;
 // bytes of ResidentArgs::diag (0: not used by this plan)
 long long resident_diag_bytes(const ResidentPlan &pl, int bytes);
@@ -413,7 +443,8 @@ struct ResidentProb {
   ResidentArgs p;
   int blk0, C;
 };
-// workgroup g works for problem tab[of[g]]; lds: the most any of them needs
+// workgroup g works for problem tab[of[g]]; lds: the most any of them needs; K: sweeps of every
+// problem (0: each its own p.K)
 template <typename T>
 void launch_resident_batch(const ResidentProb<T> *tab, const int *of, int nblocks, int lds,
                            unsigned tag0, int K, hipStream_t st);

@@ -1285,27 +1285,6 @@ __device__ __forceinline__ double dlane_from_above(double v) {
 
 enum { M64_SWEEP = 0, M64_REFRESH = 1, M64_OUTPUTS = 2 };
 
-// Arguments of every FP64 march kernel (the fields an operation does not use are unset).
-struct March64Args {
-  Grid g;
-  const uint8_t *flags;
-  Faces<double> w;
-  const float *kappa;
-  const double *s;      // state (refresh: base state s64)
-  const float *delta;   // refresh: FP32 correction added to s (nullable)
-  double *s_new;        // sweep: s + dt R; refresh: s + delta (held cells s_eq)
-  float *r0;            // refresh: R(s + delta) in FP32
-  double dt, s_in, s_eq, Da;
-  int pinned;
-  double lo, hi;        // bound check on the written state
-  double *partial;      // per block: sweep / refresh NV values, outputs NV2 values
-  int zc;
-  const int *gate;      // nullable: run only if *gate == gate_val
-  int gate_val;
-  const int *sel;       // nullable: s = pair[*sel], s_new = pair[*sel ^ 1]
-  double *pair[2];
-};
-
 template <int OP>
 struct M64Acc {
   static constexpr int K = OP == M64_OUTPUTS ? NV2 : NV;
@@ -1561,6 +1540,26 @@ __global__ void __launch_bounds__(64 * M64_ROWS) k_batch_march64(const BatchM64 
   double *part = RES ? partial + (long long)NV * w : nullptr;
   if (q.a.g.nx & 1) march64_block<1, M64_SWEEP, RES, false>(a, bx, by, bz, part);
   else march64_block<2, M64_SWEEP, RES, false>(a, bx, by, bz, part);
+}
+
+// The refreshes of the problems of a batch that ask for one (gate), items as above.
+__global__ void __launch_bounds__(64 * M64_ROWS) k_batch_refresh(const BatchR64 *__restrict__ probs,
+                                                                 const int *__restrict__ of) {
+  const int w = xcd_tile(blockIdx.x, gridDim.x);
+  const BatchR64 &q = probs[of[w]];
+  if (*q.a.gate != q.a.gate_val) return;
+  March64Args a = q.a;
+  const int c = *a.sel;
+  a.s = a.pair[c];
+  a.s_new = a.pair[c ^ 1];
+  const int L = w - q.blk0, bx = L % q.gx, by = (L / q.gx) % q.gy, bz = L / (q.gx * q.gy);
+  double *part = a.partial + (long long)NV * L;
+  if (a.g.nx & 1) march64_block<1, M64_REFRESH, true, true>(a, bx, by, bz, part);
+  else march64_block<2, M64_REFRESH, true, true>(a, bx, by, bz, part);
+}
+
+void launch_batch_refresh(const BatchR64 *probs, const int *of, int nitems, hipStream_t st) {
+  k_batch_refresh<<<nitems, dim3(64, M64_ROWS, 1), 0, st>>>(probs, of);
 }
 
 // out[NV p] = sums of problem p's item partials (items blk0 .. blk0 + nblk - 1), fixed order

@@ -523,7 +523,7 @@ RESIDENT_KERNEL k_resident_batch(const ResidentProb<T> *__restrict__ tab,
   const SweepArgs<T> a = e.a;
   ResidentArgs p = e.p;
   p.tag0 = tag0;
-  p.K = K;
+  if (K) p.K = K;
   const int b = g - e.blk0;
   if constexpr (sizeof(T) == 4) {
     switch (e.C) {
@@ -534,6 +534,15 @@ RESIDENT_KERNEL k_resident_batch(const ResidentProb<T> *__restrict__ tab,
       case 20: resident_block<T, 20, RK_PLAIN>(a, p, b); break;
       case 24: resident_block<T, 24, RK_HELD>(a, p, b); break;
       default: resident_block<T, 32, RK_HELD>(a, p, b); break;
+    }
+  } else {
+    switch (e.C) {
+      case 2: resident_block<T, 2, RK_PLAIN>(a, p, b); break;
+      case 4: resident_block<T, 4, RK_PLAIN>(a, p, b); break;
+      case 8: resident_block<T, 8, RK_PLAIN>(a, p, b); break;
+      case 10: resident_block<T, 10, RK_PLAIN>(a, p, b); break;
+      case 12: resident_block<T, 12, RK_HELD>(a, p, b); break;
+      default: resident_block<T, 16, RK_HELD>(a, p, b); break;
     }
   }
 }
@@ -574,9 +583,10 @@ static void resident_splits(const Grid &g, int bytes, int ncu, F &&take) {
         if (lds > RESIDENT_LDS || 2 * (X + Y) * C > nj * RT) continue;
         const int waves = (X * Y + 63) / 64;
         const double words = (2.0 * (X + Y) * C + 2.0 * X * Y) * gx * gy * gz * (bytes / 4);
-        ResidentPlan p{C, X, Y, gx, gy, gz, lds, (nj + 2ll) * RT * (bytes / 4), 0, 0.0};
+        ResidentPlan p{C, X, Y, gx, gy, gz, lds, (nj + 2ll) * RT * (bytes / 4), 0, 0.0,
+                       1.8e-6 * words};
         p.slot_words = p.block_words * gx * gy * gz;
-        p.us = 1.0 + 0.0075 * bytes * C * ((waves + 3) / 4) + 1.8e-6 * words +
+        p.us = 1.0 + 0.0075 * bytes * C * ((waves + 3) / 4) + p.words_us +
                (resident_lean(bytes, C) ? 1.0 : 0.0);
         take(p);
       }
@@ -686,6 +696,8 @@ void launch_resident_batch(const ResidentProb<T> *tab, const int *of, int nblock
 }
 template void launch_resident_batch<float>(const ResidentProb<float> *, const int *, int, int,
                                            unsigned, int, hipStream_t);
+template void launch_resident_batch<double>(const ResidentProb<double> *, const int *, int, int,
+                                            unsigned, int, hipStream_t);
 
 template void launch_resident<float>(const SweepArgs<float> &, const ResidentPlan &,
                                      const ResidentArgs &, hipStream_t);
