@@ -11,6 +11,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -54,12 +55,76 @@ double now_s() {
   return duration<double>(steady_clock::now().time_since_epoch()).count();
 }
 
+// Launches whose workgroups wait for each other need every one of them on the chip at once.  Two
+// such launches from two contexts (threads, streams) that do not both fit could each take part
+// of the compute units and wait for the time limit; so those in flight on a device hold at most
+// its compute units, one a workgroup, and a launch beyond that is ordered behind the oldest ones
+// by their events.  Small ones still run side by side.  Work of other streams that does end by
+// itself needs no turn, and another process's is left to the time limit.
+class Turn {
+ public:
+  Turn(int dev, int ncu, long long blocks, hipStream_t st, hipEvent_t ev)
+      : hold_(lock()), st_(st), ev_(ev) {
+    std::vector<Slot> &all = slots();
+    long long others = 0, ours = 0;      // (ours: still running before this launch can start)
+    auto take = [&](size_t i) {
+      if (all[i].st != st) (void)hipStreamWaitEvent(st, all[i].ev, 0);
+      ours += all[i].blocks;
+      all.erase(all.begin() + i);
+    };
+    for (size_t i = all.size(); i-- > 0;) {
+      if (all[i].dev != dev) continue;
+      if (all[i].st == st || all[i].ev == ev) take(i);
+      else if (ended(all[i])) all.erase(all.begin() + i);
+      else others += all[i].blocks;
+    }
+    for (size_t i = 0; i < all.size() && others + blocks > ncu;) {
+      if (all[i].dev != dev) { ++i; continue; }
+      others -= all[i].blocks;
+      take(i);
+    }
+    all.push_back(Slot{dev, std::max(blocks, ours), st, ev});
+  }
+  ~Turn() { (void)hipEventRecord(ev_, st_); }
+  Turn(const Turn &) = delete;
+  Turn &operator=(const Turn &) = delete;
+
+  // st's work is done, and it or its event goes
+  static void leave(hipStream_t st) {
+    std::lock_guard<std::mutex> hold(lock());
+    std::vector<Slot> &all = slots();
+    for (size_t i = all.size(); i-- > 0;)
+      if (all[i].st == st) all.erase(all.begin() + i);
+  }
+
+ private:
+  struct Slot {
+    int dev;
+    long long blocks;
+    hipStream_t st;
+    hipEvent_t ev;
+  };
+  static std::mutex &lock() { static std::mutex m; return m; }
+  static std::vector<Slot> &slots() { static std::vector<Slot> v; return v; }
+  // (an error that is there already is left for its own caller to see)
+  static bool ended(const Slot &s) {
+    if (hipPeekAtLastError() != hipSuccess) return false;
+    if (hipEventQuery(s.ev) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+  }
+  std::lock_guard<std::mutex> hold_;
+  hipStream_t st_;
+  hipEvent_t ev_;
+};
+
 }  // namespace
 
 struct socfv_ctx {
   Grid g{};
   hipStream_t st = nullptr;      // library stream (default priority)
   hipEvent_t ev = nullptr;
+  hipEvent_t turn = nullptr;     // of the last launch whose workgroups wait for each other
   hipEvent_t t0 = nullptr, t1 = nullptr;   // timing events around sweep chunks
   uint8_t *flags = nullptr;
   float *w32[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -464,6 +529,7 @@ struct Solver {
     ResidentArgs r = resident_args(k);
     r.fill = fill;
     r.adj = adj;
+    const Turn turn(c->dev, c->ncu, rp.blocks(), c->st, c->turn);
     launch_resident<T>(a, rp, r, c->st);
     return rp.blocks();
   }
@@ -970,7 +1036,11 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
       for (int i : set) least = std::min(least, sweeps_left[i]);
       const int rounds = least > 1e17 ? 2 : (int)std::max(1.0, std::min(4.0, std::ceil(least / K)));
       for (int r = 0; r < rounds; ++r) {
-        launch_resident_batch<float>(br.tab + (r & 1) * n, br.of, blk, lds, br.take(K, bs), K, bs);
+        const unsigned tag = br.take(K, bs);
+        {
+          const Turn turn(ctxs[0]->dev, ctxs[0]->ncu, blk, bs, ctxs[0]->turn);
+          launch_resident_batch<float>(br.tab + (r & 1) * n, br.of, blk, lds, tag, K, bs);
+        }
         launch_batch_reduce(d_probs, n, br.part, d_out, bs);
         launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_CHUNK, d_out, K, bs);
         launch_batch_refresh(br.refresh + (r & 1) * n, br.refresh_of, (int)ref_of.size(), bs);
@@ -1058,7 +1128,10 @@ void socfv_default_params(socfv_params *p) {
 
 void socfv_destroy(socfv_ctx *c) {
   if (!c) return;
-  if (c->st) (void)hipStreamSynchronize(c->st);
+  if (c->st) {
+    (void)hipStreamSynchronize(c->st);
+    Turn::leave(c->st);
+  }
   hfree(c->flags);
   for (int k = 0; k < 4; ++k) { hfree(c->w32[k]); hfree(c->w64[k]); }
   hfree(c->kappa);
@@ -1076,6 +1149,7 @@ void socfv_destroy(socfv_ctx *c) {
   for (hipEvent_t e : c->evp)
     if (e) (void)hipEventDestroy(e);
   if (c->ev) (void)hipEventDestroy(c->ev);
+  if (c->turn) (void)hipEventDestroy(c->turn);
   if (c->t0) (void)hipEventDestroy(c->t0);
   if (c->t1) (void)hipEventDestroy(c->t1);
   if (c->st) (void)hipStreamDestroy(c->st);
@@ -1112,6 +1186,7 @@ int socfv_setup_geometry(socfv_ctx **out, int nx, int ny, int nz, const uint8_t 
   auto bail = [&](int code) { socfv_destroy(c); return code; };
   if (hipStreamCreateWithFlags(&c->st, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&c->turn, hipEventDisableTiming) != hipSuccess ||
       hipEventCreate(&c->t0) != hipSuccess || hipEventCreate(&c->t1) != hipSuccess)
     return bail(fail(SOCFV_HIP_ERROR, "stream/event creation failed"));
   if (hipMalloc(&c->flags, (size_t)n) != hipSuccess ||
@@ -1510,7 +1585,10 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
         r.Da = p->Da; r.K0 = a.K; r.omega = omega; r.V = a.V;
         r.eta = a.eta;
         r.eta_new = half[a.eta == eta];
-        launch_resident_nernst(w, c->resn, r, c->st);
+        {
+          const Turn turn(c->dev, c->ncu, c->resn.blocks(), c->st, c->turn);
+          launch_resident_nernst(w, c->resn, r, c->st);
+        }
         TRY(S.resident_sums(c->resn.blocks(), c->resn, out, ran));
         if (ran) {
           a.eta = r.eta_new;
@@ -1805,6 +1883,7 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
     if (h_out) (void)hipHostFree(h_out);
     if (h_ctl) (void)hipHostFree(h_ctl);
     for (int i = 0; i < n; ++i) ctxs[i]->st = saved[i];
+    Turn::leave(bs);
     (void)hipStreamDestroy(bs);
   };
   int rc = [&]() -> int {
@@ -2222,7 +2301,11 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
                               bs));
         for (int i : set) h_ctl[i].lost = 0;
         HIPCHK(hipMemcpyAsync(d_ctl, h_ctl, sizeof(SolveCtl) * n, hipMemcpyHostToDevice, bs));
-        launch_resident_batch<double>(br.tab64, br.of, blk, lds, br.take(most, bs), 0, bs);
+        const unsigned tag = br.take(most, bs);
+        {
+          const Turn turn(ctxs[0]->dev, ctxs[0]->ncu, blk, bs, ctxs[0]->turn);
+          launch_resident_batch<double>(br.tab64, br.of, blk, lds, tag, 0, bs);
+        }
         launch_batch_reduce(d_probs, n, br.part, d_out, bs);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(h_out, d_out, sizeof(double) * NV * n, hipMemcpyDeviceToHost, bs));
@@ -2476,7 +2559,10 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
             tag = 1;
           }
           launch_flow_predict(a, c->st);
-          launch_flow_cg_whole(a, m, tag, c->st);
+          {
+            const Turn turn(c->dev, c->ncu, flow_cg_whole_blocks(a), c->st, c->turn);
+            launch_flow_cg_whole(a, m, tag, c->st);
+          }
           launch_flow_project(a, m, c->st);
           tag += 2u * m + 2u;
         }

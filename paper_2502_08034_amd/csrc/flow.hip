@@ -777,11 +777,12 @@ void launch_flow_cg_iter(const FlowArgs &a, int j, hipStream_t st) {
   k_flow_cg_a<<<a.nbc, FB, 0, st>>>(a, j);
   k_flow_cg_b<<<a.nbc, FB, 0, st>>>(a, j);
 }
+int flow_cg_whole_blocks(const FlowArgs &a) { return (a.nbc + CGW_GROUPS - 1) / CGW_GROUPS; }
 bool flow_cg_whole(const FlowArgs &a, int ncu) {
-  return a.g.n <= CGW_CELLS && (a.nbc + CGW_GROUPS - 1) / CGW_GROUPS <= ncu;
+  return a.g.n <= CGW_CELLS && flow_cg_whole_blocks(a) <= ncu;
 }
 void launch_flow_cg_whole(const FlowArgs &a, int m, unsigned tag0, hipStream_t st) {
-  k_flow_cg_whole<<<(a.nbc + CGW_GROUPS - 1) / CGW_GROUPS, CGW_LANES, 0, st>>>(a, m, tag0);
+  k_flow_cg_whole<<<flow_cg_whole_blocks(a), CGW_LANES, 0, st>>>(a, m, tag0);
 }
 void launch_flow_project(const FlowArgs &a, int cap, hipStream_t st) {
   k_flow_project<<<dim3(a.nbf, 3), FB, 0, st>>>(a, cap);

@@ -234,6 +234,7 @@ constexpr long long CGW_CELLS = 1ll << 17;       // largest box
 constexpr int CGW_BLOCKS = 512;                  // its logical blocks
 constexpr int CGW_SUMS = 4;                      // r.z, r.r, the floor's, d.q
 constexpr long long CGW_WORDS = 2 * CGW_CELLS + 2ll * CGW_SUMS * CGW_BLOCKS * (CGW_BLOCKS / 2);
+int flow_cg_whole_blocks(const FlowArgs &a);
 bool flow_cg_whole(const FlowArgs &a, int ncu);
 void launch_flow_cg_whole(const FlowArgs &a, int m, unsigned tag0, hipStream_t st);
 void launch_flow_project(const FlowArgs &a, int cap, hipStream_t st);

@@ -7,6 +7,10 @@ is a single sweep of other arithmetic); the oracle bound is that of the other FP
 see test_gpu_fp32_parity).  Boxes cover every column length, one workgroup and many, ragged
 sub-boxes in x, y and z, a top plane of one cell, and chunks of two to 401 sweeps.
 """
+import threading
+import time
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 import torch
@@ -108,6 +112,29 @@ def test_a_launch_that_is_given_up_loses_nothing(sv):
         ga, gb = sv.solve_soc_adjoint(pb.ctx, p), sv.solve_soc_adjoint(ref.ctx, p)
         assert ga[3].iterations == gb[3].iterations
         assert (ga[0] - gb[0]).abs().max() <= 1e-11 * gb[0].abs().max()
+
+
+@pytest.mark.parametrize("shape,threads", [((64, 32, 33), 6), ((175, 89, 89), 3)])
+def test_solves_of_several_threads_wait_for_their_turn(sv, shape, threads):
+    # launches that do not fit the chip together are ordered one behind the other: none runs into
+    # the time limit (1 s a launch; all the solves take less), and the results are a single
+    # thread's
+    inputs = inputs_of(shape)
+    ref = problem(sv, inputs)
+    p = sv.params(precision="fp32", tol=0.0, max_iter=2000, check_every=20, **FINITE)
+    s0, _ = sv.solve_soc_steady(ref.ctx, p)
+    pbs = [problem(sv, inputs) for _ in range(threads)]
+    start = threading.Barrier(threads)
+
+    def run(pb):
+        start.wait()
+        return [sv.solve_soc_steady(pb.ctx, p)[0] for _ in range(3)]
+
+    t0 = time.perf_counter()
+    with ThreadPoolExecutor(threads) as pool:
+        out = list(pool.map(run, pbs))
+    assert time.perf_counter() - t0 < 1.0
+    assert all(torch.equal(s, s0) for runs in out for s in runs)
 
 
 @pytest.mark.parametrize("shape,kappa,mode", [
