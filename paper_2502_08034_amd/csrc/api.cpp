@@ -2489,7 +2489,7 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
       TRY(alloc((void **)&a.code[k], sizeof(uint16_t) * (size_t)nf[k]));
       TRY(alloc((void **)&a.us[k], sizeof(double) * (size_t)nf[k]));
     }
-    double **cellv[6] = {&a.p, &a.r, &a.z, &a.q, &a.d[0], &a.d[1]};
+    double **cellv[5] = {&a.p, &a.r, &a.q, &a.d[0], &a.d[1]};
     for (double **v : cellv) TRY(alloc((void **)v, sizeof(double) * (size_t)n));
     TRY(alloc((void **)&a.ccode, (size_t)n));
     {
@@ -2572,7 +2572,7 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
             launch_flow_cg_init(a, c->st);
           }
           const int j0 = q == 0 && from > 0 ? from : 0;
-          for (int j = j0; j < std::min(m, j0 + guess); ++j) launch_flow_cg_iter(a, j, c->st);
+          for (int j = j0; j < std::min(m, j0 + guess); ++j) launch_flow_cg_iter(a, j, m, c->st);
           launch_flow_project(a, m, c->st);
         }
         HIPCHK(hipGetLastError());

@@ -76,6 +76,45 @@ __device__ __forceinline__ double sum_partials(const double *a, int n, int strid
   return block_total(v, false, sh);
 }
 
+// N such sums together (stride 1): one pass of loads and one exchange, each sum in the order of
+// sum_partials and block_total.  Their waits do not add up.
+template <int N>
+__device__ __forceinline__ void sum_partials_n(const double *const (&a)[N], int n,
+                                               double (&sh)[N][FB / 64], double (&out)[N]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < N; ++i) out[i] = 0.0;
+  constexpr int J = 4;                       // (eight would cost registers, and with them waves)
+#pragma unroll 1
+  for (int k0 = 0; k0 < n; k0 += J * FB) {
+    double t[N][J];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int k = k0 + j * FB + (int)threadIdx.x;
+        t[i][j] = a[i][k < n ? k : 0];
+        t[i][j] = k < n ? t[i][j] : 0.0;
+      }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int j = 0; j < J; ++j) out[i] += t[i][j];
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    out[i] = fwave_sum(out[i]);
+    if (lane == 0) sh[i][w] = out[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    out[i] = sh[i][0];
+#pragma unroll
+    for (int k = 1; k < FB / 64; ++k) out[i] += sh[i][k];
+  }
+}
+
 // The logical block of a workgroup (flow_order), and the place of its partials: a block's own,
 // so that every sum is taken in one order whichever workgroup does the work.
 struct Logical {
@@ -137,9 +176,11 @@ __device__ __forceinline__ PRow prow(uint8_t fl, const Grid &g, int x, int y, in
 // face, bit 7 the outlet face; 0 for fibre cells (a pore cell always has an open face or the
 // inlet: it is face-connected to the inlet).  The CG kernels need nothing else of the cell.
 constexpr unsigned CC_INLET = 64u, CC_OUTLET = 128u;
+__device__ __forceinline__ int diag_of(unsigned cc) {
+  return __popc(cc & 63u) + 2 * (int)((cc >> 6) & 1u) + 2 * (int)((cc >> 7) & 1u);
+}
 __device__ __forceinline__ PRow prow_code(unsigned cc) {
-  return PRow{(double)(__popc(cc & 63u) + 2 * ((cc >> 6) & 1u) + 2 * ((cc >> 7) & 1u)),
-              cc & 63u};
+  return PRow{(double)diag_of(cc), cc & 63u};
 }
 
 // Sum of v over the open neighbours of a cell.  Branch-free: a closed neighbour's index is
@@ -156,6 +197,43 @@ __device__ __forceinline__ double nb_sum(const double *__restrict__ v, long long
   return (((nb & 1u) ? a0 : 0.0) + ((nb & 2u) ? a1 : 0.0)) +
          (((nb & 4u) ? a2 : 0.0) + ((nb & 8u) ? a3 : 0.0)) +
          (((nb & 16u) ? a4 : 0.0) + ((nb & 32u) ? a5 : 0.0));
+}
+
+// z = r / diag.  The diagonals are the whole numbers 1 to 10, and r / n follows from RN(1 / n) by
+// one correction, exactly as the division rounds it (Markstein's theorem: the first quotient is
+// within one unit in the last place).  inv holds (1 / diag, diag) by cell code.
+struct alignas(16) InvDiag {
+  double y, n;
+};
+__device__ __forceinline__ void fill_inv(InvDiag *inv) {
+  const int n = diag_of(threadIdx.x);
+  inv[threadIdx.x] = InvDiag{n ? 1.0 / (double)n : 0.0, (double)n};
+}
+__device__ __forceinline__ double over_diag(double r, const InvDiag &v) {
+  const double q = r * v.y;
+  return fma(fma(-q, v.n, r), v.y, q);
+}
+
+// nb_sum of z = r / diag
+__device__ __forceinline__ double nb_sum_z(const double *__restrict__ r,
+                                           const uint8_t *__restrict__ code, long long c,
+                                           unsigned nb, long long sy, long long sz,
+                                           const InvDiag *inv) {
+  const long long at[6] = {(nb & 1u) ? c - 1 : c,   (nb & 2u) ? c + 1 : c,
+                           (nb & 4u) ? c - sy : c,  (nb & 8u) ? c + sy : c,
+                           (nb & 16u) ? c - sz : c, (nb & 32u) ? c + sz : c};
+  double v[6];
+  unsigned cc[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    v[k] = r[at[k]];
+    cc[k] = code[at[k]];
+  }
+#pragma unroll
+  for (int k = 0; k < 6; ++k) v[k] = over_diag(v[k], inv[cc[k]]);
+  return (((nb & 1u) ? v[0] : 0.0) + ((nb & 2u) ? v[1] : 0.0)) +
+         (((nb & 4u) ? v[2] : 0.0) + ((nb & 8u) ? v[3] : 0.0)) +
+         (((nb & 16u) ? v[4] : 0.0) + ((nb & 32u) ? v[5] : 0.0));
 }
 
 // ---- face classification ---------------------------------------------------------------
@@ -241,7 +319,7 @@ __global__ void __launch_bounds__(FB) k_flow_predict(FlowArgs a) {
 }
 
 // ---- pressure CG -------------------------------------------------------------------------
-// init: r = b - A p with b = D gbc - D u* / dt, z = r / diag; partials of r.z, r.r into
+// init: r = b - A p with b = D gbc - D u* / dt; partials of r.z, r.r (z = r / diag) into
 // parity 0.  Block 0 also sets the step's stop target from the last projection's partials.
 __global__ void __launch_bounds__(FB) k_flow_cg_init(FlowArgs a) {
   __shared__ double sh[FB / 64];
@@ -261,7 +339,7 @@ __global__ void __launch_bounds__(FB) k_flow_cg_init(FlowArgs a) {
   for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
        c += (long long)gridDim.x * FB) {
     const unsigned cc = a.ccode[c];
-    double rv = 0.0, zv = 0.0;
+    double rv = 0.0;
     if (cc) {
       // x faces: index c + (y + ny z); y faces: c + nx z
       const unsigned row = (unsigned)c / (unsigned)g.nx, z = row / (unsigned)g.ny;
@@ -273,14 +351,13 @@ __global__ void __launch_bounds__(FB) k_flow_cg_init(FlowArgs a) {
       const PRow pr = prow_code(cc);
       const double ap = pr.diag * a.p[c] - nb_sum(a.p, c, pr.nb, sy, sz);
       rv = b - ap;
-      zv = rv / pr.diag;
+      const double zv = rv / pr.diag;
       rz += rv * zv;
       rr += rv * rv;
       const double dp = pr.diag * a.p[c];
       fl += b * b + dp * dp;
     }
     a.r[c] = rv;
-    a.z[c] = zv;
   }
   rz = block_total(rz, false, sh);
   rr = block_total(rr, false, sh);
@@ -299,42 +376,63 @@ __global__ void __launch_bounds__(FB) k_flow_cg_init(FlowArgs a) {
 // (the step's fixed point does not depend on it).
 constexpr double CG_FLOOR = 16.0;
 
-// iteration j, first half: stop test; d = z + beta d_old; q = A d; partials of d.q
+// Both halves of an iteration are bound by memory.  So z is not stored but taken from r wherever
+// it is needed, and p, which nothing reads before the step's end, is advanced by the first half of
+// the next iteration, which reads d anyway: 74 bytes a cell and iteration against 90, and
+// 51.5 + 21.4 us on 256 x 128 x 128 (34 MB a vector; 4.0 and 4.9 TB/s) against 43 + 41.  More
+// waves per SIMD (6, 8) and the cell codes loaded a turn ahead changed nothing.  A step's last
+// p update is made by the first half that finds the target met, or, in iteration cap - 1 (which
+// no first half follows), by the second half itself.
+
+// iteration j, first half: p += alpha d_old (of iteration j - 1); stop test; d = z + beta d_old;
+// q = A d; partials of d.q.  (FS_DONE is j + 1 once a block of this launch has found the target
+// met: the others still have to advance p.)
 __global__ void __launch_bounds__(FB) k_flow_cg_a(FlowArgs a, int j) {
-  __shared__ double sh[FB / 64];
-  if (a.sc[FS_DONE] != 0.0 || a.sc[FS_STALL] != 0.0) return;
+  __shared__ double sh[FB / 64], sh4[4][FB / 64];
+  __shared__ InvDiag inv[256];
+  const double done = a.sc[FS_DONE];
+  if ((done != 0.0 && done != (double)(j + 1)) || a.sc[FS_STALL] != 0.0) return;
   const Grid g = a.g;
   const Logical me = logical(a.corder);
   const int par = j & 1;
-  const double rz = sum_partials(a.prz[par], a.nbc, 1, sh);
-  const double rr = sum_partials(a.prr[par], a.nbc, 1, sh);
+  fill_inv(inv);
+  const long long c0 = (long long)me.lb * FB + threadIdx.x, stride = (long long)gridDim.x * FB;
+  double s[4];
+  sum_partials_n<4>({a.prz[par], a.prr[par], a.pfl, a.prz[par ^ 1]}, a.nbc, sh4, s);
+  const double rz = s[0], rr = s[1], alpha = a.sc[FS_ALPHA];
   const double floor2 = (CG_FLOOR * 2.220446049250313e-16) * (CG_FLOOR * 2.220446049250313e-16) *
-                        sum_partials(a.pfl, a.nbc, 1, sh);
+                        s[2];
+  const double *__restrict__ dold = a.d[par ^ 1];
   if (rr <= fmax(a.sc[FS_TARGET], floor2)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[FS_DONE] = 1.0;
+    if (j > 0)
+      for (long long c = c0; c < g.n; c += stride)
+        if (a.ccode[c]) a.p[c] += alpha * dold[c];
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[FS_DONE] = (double)(j + 1);
     return;
   }
-  const double beta = j == 0 ? 0.0 : rz / sum_partials(a.prz[par ^ 1], a.nbc, 1, sh);
-  const double *__restrict__ zz = a.z;
-  const double *__restrict__ dold = a.d[par ^ 1];
+  const double beta = j == 0 ? 0.0 : rz / s[3];
+  const double *__restrict__ r = a.r;
+  const uint8_t *__restrict__ code = a.ccode;
   double *__restrict__ dn = a.d[par];
   const long long sy = g.nx, sz = (long long)g.nx * g.ny;
   double dq = 0.0;
-  for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
-       c += (long long)gridDim.x * FB) {
-    const unsigned cc = a.ccode[c];
+  for (long long c = c0; c < g.n; c += stride) {
+    const unsigned cc = code[c];
     double dv = 0.0, qv = 0.0;
     if (cc) {
-      const PRow pr = prow_code(cc);
+      const unsigned nb = cc & 63u;
+      const InvDiag own = inv[cc];
       double nbs;
+      dv = over_diag(r[c], own);
       if (j == 0) {
-        dv = zz[c];
-        nbs = nb_sum(zz, c, pr.nb, sy, sz);
+        nbs = nb_sum_z(r, code, c, nb, sy, sz, inv);
       } else {
-        dv = zz[c] + beta * dold[c];
-        nbs = nb_sum(zz, c, pr.nb, sy, sz) + beta * nb_sum(dold, c, pr.nb, sy, sz);
+        const double dc = dold[c], pv = a.p[c];
+        nbs = nb_sum_z(r, code, c, nb, sy, sz, inv) + beta * nb_sum(dold, c, nb, sy, sz);
+        a.p[c] = pv + alpha * dc;
+        dv = dv + beta * dc;
       }
-      qv = pr.diag * dv - nbs;
+      qv = own.n * dv - nbs;
       dq += dv * qv;
     }
     dn[c] = dv;
@@ -344,29 +442,29 @@ __global__ void __launch_bounds__(FB) k_flow_cg_a(FlowArgs a, int j) {
   if (threadIdx.x == 0) a.pdq[me.slot] = dq;
 }
 
-// iteration j, second half: alpha = r.z / d.q; p += alpha d; r -= alpha q; z = r / diag;
-// partials of the new r.z, r.r into the other parity
-__global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j) {
-  __shared__ double sh[FB / 64];
+// iteration j, second half: alpha = r.z / d.q; r -= alpha q; partials of the new r.z, r.r
+// (z = r / diag) into the other parity.  last: nothing follows, so p += alpha d here
+__global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j, bool last) {
+  __shared__ double sh[FB / 64], sh2[2][FB / 64];
+  __shared__ InvDiag inv[256];
   if (a.sc[FS_DONE] != 0.0 || a.sc[FS_STALL] != 0.0) return;
   const Grid g = a.g;
   const Logical me = logical(a.corder);
   const int par = j & 1;
-  const double rz = sum_partials(a.prz[par], a.nbc, 1, sh);
-  const double dq = sum_partials(a.pdq, a.nbc, 1, sh);
-  const double alpha = rz / dq;
+  fill_inv(inv);
+  const long long c0 = (long long)me.lb * FB + threadIdx.x, stride = (long long)gridDim.x * FB;
+  double s[2];
+  sum_partials_n<2>({a.prz[par], a.pdq}, a.nbc, sh2, s);
+  const double alpha = s[0] / s[1];
   const double *__restrict__ dn = a.d[par];
   double rzn = 0.0, rrn = 0.0;
-  for (long long c = (long long)me.lb * FB + threadIdx.x; c < g.n;
-       c += (long long)gridDim.x * FB) {
+  for (long long c = c0; c < g.n; c += stride) {
     const unsigned cc = a.ccode[c];
     if (!cc) continue;
-    const PRow pr = prow_code(cc);
-    a.p[c] += alpha * dn[c];
+    if (last) a.p[c] += alpha * dn[c];
     const double rv = a.r[c] - alpha * a.q[c];
-    const double zv = rv / pr.diag;
+    const double zv = over_diag(rv, inv[cc]);
     a.r[c] = rv;
-    a.z[c] = zv;
     rzn += rv * zv;
     rrn += rv * rv;
   }
@@ -375,7 +473,10 @@ __global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j) {
   if (threadIdx.x == 0) {
     a.prz[par ^ 1][me.slot] = rzn;
     a.prr[par ^ 1][me.slot] = rrn;
-    if (blockIdx.x == 0) a.sc[FS_CG_STEP] = (double)(j + 1);
+    if (blockIdx.x == 0) {
+      a.sc[FS_CG_STEP] = (double)(j + 1);
+      a.sc[FS_ALPHA] = alpha;
+    }
   }
 }
 
@@ -773,9 +874,9 @@ void launch_flow_predict(const FlowArgs &a, hipStream_t st) {
 void launch_flow_cg_init(const FlowArgs &a, hipStream_t st) {
   k_flow_cg_init<<<a.nbc, FB, 0, st>>>(a);
 }
-void launch_flow_cg_iter(const FlowArgs &a, int j, hipStream_t st) {
+void launch_flow_cg_iter(const FlowArgs &a, int j, int cap, hipStream_t st) {
   k_flow_cg_a<<<a.nbc, FB, 0, st>>>(a, j);
-  k_flow_cg_b<<<a.nbc, FB, 0, st>>>(a, j);
+  k_flow_cg_b<<<a.nbc, FB, 0, st>>>(a, j, j == cap - 1);
 }
 int flow_cg_whole_blocks(const FlowArgs &a) { return (a.nbc + CGW_GROUPS - 1) / CGW_GROUPS; }
 bool flow_cg_whole(const FlowArgs &a, int ncu) {

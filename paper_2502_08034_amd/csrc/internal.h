@@ -196,10 +196,11 @@ void launch_nernst(const NernstArgs &a, const Tiles &t, hipStream_t st);
 // outlet plane (zero gradient), 1 open, 2 closed along the face normal, 3 wall across it.
 constexpr uint16_t FC_OPEN = 0x8000;
 // Scalar slots of the flow step (device doubles after the partials)
-// (FS_DONE: the step's CG met its target; FS_CG_STEP its iterations; FS_STALL: a step ran out of
-// launched CG iterations, and everything enqueued after it returns at once)
+// (FS_DONE: nonzero once the step's CG has met its target; FS_CG_STEP its iterations; FS_ALPHA the
+// last one's alpha; FS_STALL: a step ran out of launched CG iterations, and everything enqueued
+// after it returns at once)
 enum FlowSlot { FS_TARGET = 0, FS_DONE = 1, FS_CG_STEP = 2, FS_CG_TOTAL = 3, FS_STEPS = 4,
-                FS_STALL = 5, FS_N = 6 };
+                FS_STALL = 5, FS_ALPHA = 6, FS_N = 7 };
 struct FlowArgs {
   Grid g;
   const uint8_t *flags;
@@ -207,7 +208,7 @@ struct FlowArgs {
   uint8_t *ccode;        // per cell: open-neighbour mask | inlet (64) | outlet (128); 0 = fibre
   double *u[3];          // velocity (updated in place by the projection)
   double *us[3];         // predictor output u*
-  double *p, *r, *z, *q, *d[2];   // pressure and CG vectors (cells)
+  double *p, *r, *q, *d[2];       // pressure and CG vectors (cells)
   double dt, p_in, theta2;        // theta2: (CG stop factor)^2
   int nbc, nbf;          // blocks of the cell kernels / per face array of the face kernels
   int *corder, *forder[3];        // logical block of each workgroup (flow_order)
@@ -227,7 +228,8 @@ void flow_order(long long plane, int nb, int *order);
 void launch_flow_codes(const FlowArgs &a, hipStream_t st);
 void launch_flow_predict(const FlowArgs &a, hipStream_t st);
 void launch_flow_cg_init(const FlowArgs &a, hipStream_t st);
-void launch_flow_cg_iter(const FlowArgs &a, int j, hipStream_t st);   // both CG kernels
+// both CG kernels of iteration j of at most cap
+void launch_flow_cg_iter(const FlowArgs &a, int j, int cap, hipStream_t st);
 // cap: CG iterations after which a step goes on without having met its target
 // a step's CG (cg_init included) in one launch of up to m iterations; 2 m + 2 tags from tag0
 constexpr long long CGW_CELLS = 1ll << 17;       // largest box
