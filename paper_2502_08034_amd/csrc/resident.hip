@@ -564,7 +564,9 @@ constexpr int RES_C32[] = {4, 8, 12, 16, 20, 24, 32}, RES_C64[] = {2, 4, 8, 10, 
 // Every split of a box over at most ncu workgroups with its time per sweep.  The model, fitted
 // to splits of 65 thousand to 4.2 million cells (within a tenth): 1 us for the exchange's latency
 // and the barriers, 0.06 us per cell of a full block's columns (0.12 in FP64), 1.8 us per million
-// exchanged words, and 1 us more for lean columns.
+// exchanged words, and more for lean columns: 1.6 us in FP32 (256 x 128 x 128 and batches of
+// C = 32 take 6 us; at 1.0 the batched solves chose them too often: twelve boxes of mixed sizes
+// 136.5 ms against 132.0) and 1.0 in FP64 (at 1.6 their polish took 7.55 ms, not 7.25).
 template <typename F>
 static void resident_splits(const Grid &g, int bytes, int ncu, F &&take) {
   const int *const Cs = bytes == 4 ? RES_C32 : RES_C64;
@@ -587,7 +589,7 @@ static void resident_splits(const Grid &g, int bytes, int ncu, F &&take) {
                        1.8e-6 * words};
         p.slot_words = p.block_words * gx * gy * gz;
         p.us = 1.0 + 0.0075 * bytes * C * ((waves + 3) / 4) + p.words_us +
-               (resident_lean(bytes, C) ? 1.0 : 0.0);
+               (resident_lean(bytes, C) ? (bytes == 4 ? 1.6 : 1.0) : 0.0);
         take(p);
       }
     }
