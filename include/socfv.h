@@ -214,8 +214,10 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
 
 /*
  * Many problems (contexts with geometry and velocity set; uneven sizes allowed) solved
- * together.  With every p[i].precision == SOCFV_FP32, each FP32 sweep is one launch over
- * a tile work list spanning all unfinished problems (persistent blocks taking tiles from a
+ * together.  With every p[i].precision == SOCFV_FP32, problems that fit the chip share resident
+ * launches, a chunk of check_every sweeps each, several problems at a time (chosen anew as
+ * problems finish), and so does the FP64 polish.  For the others each FP32 sweep is one launch
+ * over a tile work list spanning them (persistent blocks taking tiles from a
  * device counter), and each problem keeps its own dt, tau, FP64 refreshes and stopping rule
  * (its own p[i]), all decided on the device: one chunk of check_every sweeps (rounded up to
  * a multiple of 4) with the work lists, the per-problem residuals and decisions and the

@@ -356,7 +356,11 @@ int unconnected_on_host(socfv_ctx *c, long long *missing) {
 int unconnected(socfv_ctx *c, long long *missing) {
   const long long n = c->g.n;
   if (n >= (1ll << 31) - 1) return unconnected_on_host(c, missing);
-  if (!c->s32[0]) HIPCHK(hipMalloc(&c->s32[0], sizeof(int) * (size_t)(n + 1)));
+  if (!c->s32[0] && hipMalloc(&c->s32[0], sizeof(int) * (size_t)(n + 1)) != hipSuccess) {
+    (void)hipGetLastError();               // no room: the host's memory serves
+    c->s32[0] = nullptr;
+    return unconnected_on_host(c, missing);
+  }
   const int nb = flags_blocks(c->g);
   launch_connect(c->g, c->flags, (int *)c->s32[0], c->partial, nb, c->st);
   HIPCHK(hipGetLastError());
