@@ -514,7 +514,9 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
   __shared__ double sh[CGW_GROUPS][FB / 64];
   __shared__ double zl[CGW_LANES], part[3][CGW_GROUPS];
   __shared__ int slots[CGW_GROUPS];
-  __shared__ int dead;
+  // a wait of a sum / of z's words ran into its limit: two flags, so that between a barrier and
+  // the reading of one of them no wave that is ahead can raise it
+  __shared__ int dead_sum, dead_z;
   if (a.sc[FS_STALL] != 0.0) return;
   const Grid g = a.g;
   const int grp = threadIdx.x / FB, t = threadIdx.x % FB;
@@ -526,15 +528,17 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
   const int run = lb < long8 ? lb / (q8 + 1) : r8 + (lb - long8) / max(q8, 1);
   if (t == 0) slots[grp] = 8 * (lb < long8 ? lb % (q8 + 1) : (lb - long8) % max(q8, 1)) + run;
   const int nb = gridDim.x;
-  if (threadIdx.x == 0) dead = 0;
+  if (threadIdx.x == 0) dead_sum = dead_z = 0;
   unsigned long long *const zw = a.words, *const pw = a.words + 2 * CGW_CELLS;
 
-  // waits until every word this lane asks for is there
-  auto wait = [&](auto &&all) {
+  // waits until every word this lane asks for is there (a limit below 0.1 ms is looked at on every
+  // turn: 256 of them take longer)
+  const unsigned turns = a.limit < 10000 ? 0u : 255u;
+  auto wait = [&](int &dead, auto &&all) {
     unsigned spins = 0;
     unsigned long long t0 = 0;
     while (!all()) {
-      if (a.limit == 0 || (++spins & 255u) == 0) {
+      if ((++spins & turns) == 0) {
         const unsigned long long now = wall_clock64();
         if (t0 == 0) t0 = now;
         if (now - t0 >= a.limit ||
@@ -569,7 +573,7 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
 #pragma unroll 1
       for (int i = t; i < a.nbc; i += FB) {
         double x[N];
-        wait([&] {
+        wait(dead_sum, [&] {
           bool ok = true;
 #pragma unroll
           for (int k = 0; k < N; ++k)
@@ -637,7 +641,7 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
 #pragma unroll
   for (int k = 0; k < 6; ++k) dn[k] = 0.0;
   int j = 0;
-  bool done = false;
+  bool gone = false;                         // (the same in every lane)
   for (;; ++j) {
     const unsigned tag = tag0 + 2u * (unsigned)j;
     // the cells' z and the sums of the residual
@@ -652,17 +656,13 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
       tot[0] = two[0];
       tot[1] = two[1];
     }
-    if (dead) break;
-    if (j >= m) break;
-    if (tot[1] <= fmax(target, floor2)) {
-      done = true;
-      break;
-    }
+    gone = dead_sum != 0;
+    if (gone || j >= m || tot[1] <= fmax(target, floor2)) break;
     // d = z + beta d, q = A d (k_flow_cg_a)
     const double beta = j == 0 ? 0.0 : tot[0] / rz_old;
     double zn[6];
     if (far)
-      wait([&] {
+      wait(dead_z, [&] {
         // both z neighbours' words in flight at once (a near one reads this cell's); x and y
         // neighbours are far only at the ends of the workgroup's run of cells
         bool ok = true;
@@ -702,7 +702,8 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
     }
     dq[0] = group_total(dq[0], sh);
     share(dq, tag + 1u, 3);
-    if (dead) break;
+    gone = dead_sum != 0 || dead_z != 0;
+    if (gone) break;
     // the update (k_flow_cg_b)
     const double alpha = tot[0] / dq[0];
     rz_old = tot[0];
@@ -717,12 +718,10 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
     tot[0] = group_total(rzn, sh);
     tot[1] = group_total(rrn, sh);
   }
-  __syncthreads();
-  if (dead) {
+  if (gone) {
     if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[FS_STALL] = 2.0;
     return;
   }
-  (void)done;
   if (cc) a.p[c] = p;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.sc[FS_CG_STEP] = (double)j;

@@ -188,3 +188,18 @@ def test_cg_in_one_launch_equals_the_separate_kernels(sv, shape):
         assert a[4].steps == b[4].steps == 60 and a[4].cg_iterations == b[4].cg_iterations
         for x, y in zip(a[:4], b[:4]):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("limit", [0.0, 1e-7, 5e-7, 1e-6, 2e-6, 4e-6, 8e-6])
+def test_a_single_launch_cg_may_give_up_in_any_exchange(sv, limit):
+    # a wait limit about as long as an exchange: workgroups give up in the sums and in the
+    # neighbours' values alike, some of a workgroup's waves before others; every launch ends and
+    # the separate kernels take the steps to their number
+    g = I.fibres_nonoverlap(96, 50, 54, 2.5, 0.88, 11)
+    ctx = sv.setup_geometry(torch.as_tensor(g.solid, device="cuda"))
+    sv.set_wait_limit(ctx, limit)
+    for cap in (1, 3, 40):
+        ux, uy, uz, p, st = sv.solve_stokes(ctx, cfl=3.0, max_steps=20, tol=0.0, cg_max=cap,
+                                            want_pressure=True)
+        assert st.steps == 20 and 0 < st.cg_iterations <= 20 * cap
+        assert all(bool(torch.isfinite(v).all()) for v in (ux, uy, uz, p))
