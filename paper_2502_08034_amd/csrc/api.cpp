@@ -2567,6 +2567,7 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
             const Turn turn(c->dev, c->ncu, flow_cg_whole_blocks(a), c->st, c->turn);
             launch_flow_cg_whole(a, m, tag, c->st);
           }
+          std::swap(a.p, a.q);
           launch_flow_project(a, m, c->st);
           tag += 2u * m + 2u;
         }
@@ -2585,7 +2586,10 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
         const long ran = (long)c->hres[FS_STEPS] - steps - s;
         s += ran;
         if (c->hres[FS_STALL] == 2.0) {
-          whole = false;                 // given up: the step again, in separate launches
+          // given up: the step again, in separate launches, from the pressure before it
+          if ((grp - ran) & 1) std::swap(a.p, a.q);
+          whole = false;
+          a.lost = nullptr;
           launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
         } else if (c->hres[FS_STALL] != 0.0) {
           from = (int)c->hres[FS_CG_STEP];

@@ -492,8 +492,11 @@ __global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j, bool last) 
 // after a sum that its readers have contributed to since they read it, so one slot per word is
 // enough: z and the residual's sums after d.q's, d.q's after the residual's (which therefore
 // have words of their own).  Waits
-// end at a time limit as in the resident sweeps: FS_STALL is then 2, nothing has been written,
-// and the host repeats the step with the separate kernels.
+// end at a time limit as in the resident sweeps.  A workgroup can give up in the very last sum, to
+// which it has contributed, and the others then come to the end; so whether a launch counts is
+// decided behind it, by the projection: the new pressure goes to q, and `lost` (raised by any
+// workgroup that gave up) makes FS_STALL 2 and the host repeat the step from the old pressure with
+// the separate kernels.
 constexpr int CGW_GROUPS = 2, CGW_LANES = CGW_GROUPS * FB;
 
 // Sum over a group of 256 lanes, as block_total over a block of them.
@@ -609,7 +612,7 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
   }
   const unsigned cc = c < g.n ? a.ccode[c] : 0u;
   const PRow pr = prow_code(cc);
-  double p = 0.0, r = 0.0, z = 0.0;
+  double p = c < g.n ? a.p[c] : 0.0, r = 0.0, z = 0.0;
   double tot[3] = {0.0, 0.0, 0.0};           // r.z, r.r, the floor's sum
   if (cc) {
     const unsigned row = (unsigned)c / (unsigned)g.nx, zz = row / (unsigned)g.ny;
@@ -618,7 +621,6 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
     const double div = (a.us[0][ix + 1] - a.us[0][ix]) + (a.us[1][iy + g.nx] - a.us[1][iy]) +
                        (a.us[2][c + sz] - a.us[2][c]);
     const double b = ((cc & CC_INLET) ? 2.0 * a.p_in : 0.0) - div / a.dt;
-    p = a.p[c];
     const double ap = pr.diag * p - nb_sum(a.p, c, pr.nb, sy, sz);
     r = b - ap;
     z = r / pr.diag;
@@ -718,11 +720,8 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
     tot[0] = group_total(rzn, sh);
     tot[1] = group_total(rrn, sh);
   }
-  if (gone) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.sc[FS_STALL] = 2.0;
-    return;
-  }
-  if (cc) a.p[c] = p;
+  if (gone) return;
+  if (c < g.n) a.q[c] = p;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     a.sc[FS_CG_STEP] = (double)j;
     a.sc[FS_DONE] = 1.0;
@@ -732,10 +731,15 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
 // ---- projection: u' = u* - dt (G p + gbc); partials [sum (u' - u)^2, sum u'^2] -----------
 // A step whose CG has neither met its target nor reached the cap has run out of launched
 // iterations: nothing is projected, and the launches behind this one return until the host has
-// enqueued more (the decision is the same in every block: none writes what it reads).
+// enqueued more (the decision is the same in every block: none writes what it reads).  The same
+// where the whole CG was given up.
 __global__ void __launch_bounds__(FB) k_flow_project(FlowArgs a, int cap) {
   __shared__ double sh[FB / 64];
   if (a.sc[FS_STALL] != 0.0) return;
+  if (a.lost && *a.lost) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.sc[FS_STALL] = 2.0;
+    return;
+  }
   if (a.sc[FS_DONE] == 0.0 && a.sc[FS_CG_STEP] < (double)cap) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.sc[FS_STALL] = 1.0;
     return;

@@ -197,8 +197,8 @@ void launch_nernst(const NernstArgs &a, const Tiles &t, hipStream_t st);
 constexpr uint16_t FC_OPEN = 0x8000;
 // Scalar slots of the flow step (device doubles after the partials)
 // (FS_DONE: nonzero once the step's CG has met its target; FS_CG_STEP its iterations; FS_ALPHA the
-// last one's alpha; FS_STALL: a step ran out of launched CG iterations, and everything enqueued
-// after it returns at once)
+// last one's alpha; FS_STALL: a step ran out of launched CG iterations (1) or its whole CG was given
+// up (2), and everything enqueued after it returns at once)
 enum FlowSlot { FS_TARGET = 0, FS_DONE = 1, FS_CG_STEP = 2, FS_CG_TOTAL = 3, FS_STEPS = 4,
                 FS_STALL = 5, FS_ALPHA = 6, FS_N = 7 };
 struct FlowArgs {
@@ -213,7 +213,8 @@ struct FlowArgs {
   int nbc, nbf;          // blocks of the cell kernels / per face array of the face kernels
   int *corder, *forder[3];        // logical block of each workgroup (flow_order)
   unsigned long long *words;      // exchange words of the whole CG (CGW_WORDS)
-  int *lost;                      // raised when a wait of the whole CG ran into its limit
+  int *lost;                      // raised when a wait of the whole CG ran into its limit (null:
+                                  // separate kernels)
   unsigned long long limit;       // that limit, in ticks of the 100 MHz clock
   double *prz[2], *prr[2], *pdq;  // per-block CG partials (cell kernels), ping-pong by parity
   double *pdu;           // per-block [sum du^2, sum u^2] of the projection, (3 nbf) x 2
@@ -230,8 +231,8 @@ void launch_flow_predict(const FlowArgs &a, hipStream_t st);
 void launch_flow_cg_init(const FlowArgs &a, hipStream_t st);
 // both CG kernels of iteration j of at most cap
 void launch_flow_cg_iter(const FlowArgs &a, int j, int cap, hipStream_t st);
-// cap: CG iterations after which a step goes on without having met its target
-// a step's CG (cg_init included) in one launch of up to m iterations; 2 m + 2 tags from tag0
+// a step's CG (cg_init included) in one launch of up to m iterations, from the pressure p to the
+// pressure q; 2 m + 2 tags from tag0
 constexpr long long CGW_CELLS = 1ll << 17;       // largest box
 constexpr int CGW_BLOCKS = 512;                  // its logical blocks
 constexpr int CGW_SUMS = 4;                      // r.z, r.r, the floor's, d.q
@@ -239,6 +240,7 @@ constexpr long long CGW_WORDS = 2 * CGW_CELLS + 2ll * CGW_SUMS * CGW_BLOCKS * (C
 int flow_cg_whole_blocks(const FlowArgs &a);
 bool flow_cg_whole(const FlowArgs &a, int ncu);
 void launch_flow_cg_whole(const FlowArgs &a, int m, unsigned tag0, hipStream_t st);
+// cap: CG iterations after which a step goes on without having met its target
 void launch_flow_project(const FlowArgs &a, int cap, hipStream_t st);
 void launch_flow_check(const FlowArgs &a, hipStream_t st);   // fills pdiv
 

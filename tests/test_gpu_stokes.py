@@ -203,3 +203,25 @@ def test_a_single_launch_cg_may_give_up_in_any_exchange(sv, limit):
                                             want_pressure=True)
         assert st.steps == 20 and 0 < st.cg_iterations <= 20 * cap
         assert all(bool(torch.isfinite(v).all()) for v in (ux, uy, uz, p))
+
+
+@pytest.mark.parametrize("shape", [(48, 32, 32), (96, 50, 54)])
+def test_a_given_up_cg_leaves_no_trace(sv, shape):
+    # wherever a launch is given up, in the last sum of a CG too (where other workgroups of the
+    # launch come to the end), the step starts again from the old pressure: the flow is that of
+    # the separate kernels bit for bit (wait limit 0 gives up the first launch)
+    g = I.fibres_nonoverlap(*shape, 2.5, 0.88, 11)
+    solid = torch.as_tensor(g.solid, device="cuda")
+    start = None
+    for cap in (1, 2, 30):
+        kw = dict(cfl=3.0, max_steps=25, check_every=10, tol=0.0, cg_max=cap, want_pressure=True)
+        want = None
+        for k in range(24):
+            ctx = sv.setup_geometry(solid)
+            sv.set_wait_limit(ctx, 2.5e-7 * k)
+            got = sv.solve_stokes(ctx, start=start and [v.clone() for v in start], **kw)
+            want = want or got
+            assert got[4].steps == 25 and got[4].cg_iterations == want[4].cg_iterations, (cap, k)
+            for a, b in zip(got[:4], want[:4]):
+                assert torch.equal(a, b), (cap, k)
+        start = want[:4]
