@@ -281,7 +281,8 @@ int ensure_state(socfv_ctx *c) {
   return ensure_partial(c, partial_need(c->g, c->tiles));
 }
 
-// The resident splits of this problem with their exchange buffer, if the box fits the chip.
+// The resident splits of this problem with their exchange buffer, if the box fits the chip (after
+// ensure_state).
 int ensure_resident(socfv_ctx *c) {
   if (!c->res_planned) {
     c->res_planned = true;
@@ -309,8 +310,10 @@ int ensure_resident(socfv_ctx *c) {
     c->res.C = c->res64.C = c->resn.C = 0;   // no room: the other launches need none
     return 0;
   }
-  // words of an earlier buffer at this address could carry a tag of this one
+  // words of an earlier buffer at this address could carry a tag of this one.  The flag of a
+  // given-up launch is clear between calls: from here on whoever finds it raised clears it.
   launch_fill_f64((double *)c->inbox, c->inbox_words, 0.0, c->st);
+  launch_fill_f32((float *)&c->dctl->lost, 1, 0.0f, c->st);
   HIPCHK(hipGetLastError());
   c->tag = 1;
   return ensure_partial(c, NV * blocks + 64);
@@ -552,15 +555,9 @@ struct Solver {
     ran = !c->hctl->lost;
     if (!ran) {
       plan.C = 0;
-      TRY(clear_ctl());
+      launch_fill_f32((float *)&c->dctl->lost, 1, 0.0f, c->st);
+      HIPCHK(hipGetLastError());
     }
-    return 0;
-  }
-
-  int clear_ctl() {
-    *c->hctl = SolveCtl{};
-    HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
-    HIPCHK(hipStreamSynchronize(c->st));
     return 0;
   }
 
@@ -787,7 +784,6 @@ struct Solver {
   int solve(const double *s_init, double *res_final, int *state_buf) {
     TRY(setup());
     TRY(ensure_resident(c));
-    TRY(clear_ctl());
     const long long n = c->g.n;
     launch_init_state(c->g, c->flags, s_init, p->s_in, p->s_eq, pinned, c->s64[0], c->st);
     HIPCHK(hipGetLastError());
@@ -1403,7 +1399,6 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
   Solver S{c, p};
   TRY(S.setup());
   TRY(ensure_resident(c));
-  TRY(S.clear_ctl());
   const long long n = c->g.n;
   const int pinned = p->mode == SOCFV_PINNED;
   // g_P = w_out,P / (Q_out (s_eq - s_in)); Q_out from the outputs of the forward state
@@ -1561,7 +1556,6 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
     Solver S{c, &pt};
     TRY(S.setup());
     TRY(ensure_resident(c));
-    TRY(S.clear_ctl());
     const bool whole = c->resn.C > 0 && c->inbox && !c->tiles_fixed;
     // the overpotentials; the resident iteration reads one half and writes the other
     HIPCHK(hipMalloc(&eta, sizeof(double) * (size_t)n * (whole ? 2 : 1)));

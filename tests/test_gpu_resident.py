@@ -231,3 +231,27 @@ def test_resident_nernst_equals_the_launches(sv, shape, kappa):
     sv.set_wait_limit(fresh.ctx, 0.0)            # given up: the launches go on
     s3, e3, _ = sv.solve_nernst(fresh.ctx, p, omega=0.3, want_eta=True)
     assert (s3 - s2).abs().max() <= 1e-12 and (e3 - e2).abs().max() <= 1e-11
+
+
+def test_given_up_launches_of_one_kind_leave_the_others(sv):
+    # an FP32 solve, an FP64 solve, an adjoint and a Nernst solve on one context, each given up
+    # once (the flag that says so is cleared by whoever finds it), then all four again with the
+    # ordinary limit: the results of a context on which nothing was given up, to the FP64 sweeps'
+    # rounding
+    inputs = inputs_of((96, 48, 40))
+    ref, pb = problem(sv, inputs), problem(sv, inputs)
+    kw = dict(tol=0.0, max_iter=300, check_every=100)
+    p32, p64 = (sv.params(precision=v, **kw, **FINITE) for v in ("fp32", "fp64"))
+    pn = sv.params(s_in=0.2, s_eq=0.7, Da=5.0, mode=0, **kw)
+
+    def kinds(ctx):
+        yield sv.solve_soc_steady(ctx, p32)[0]
+        yield sv.solve_soc_steady(ctx, p64)[0]
+        yield sv.solve_soc_adjoint(ctx, p64, want_psi=True)[2]
+        yield sv.solve_nernst(ctx, pn, omega=0.3)[0]
+
+    want = list(kinds(ref.ctx))
+    for limit in (0.0, 1.0):
+        sv.set_wait_limit(pb.ctx, limit)
+        for k, (a, b) in enumerate(zip(kinds(pb.ctx), want)):
+            assert (a - b).abs().max() <= 1e-12 * max(1.0, float(b.abs().max())), (limit, k)
