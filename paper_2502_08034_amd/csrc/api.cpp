@@ -509,8 +509,8 @@ struct Solver {
     return sizeof(T) == 4 ? c->res : c->res64;
   }
   template <typename T>
-  bool resident() const {
-    return res_plan<T>().C > 0 && c->inbox && !c->tiles_fixed;
+  bool resident(long k) const {          // a chunk of k sweeps
+    return k >= RESIDENT_LEAST && res_plan<T>().C > 0 && c->inbox && !c->tiles_fixed;
   }
 
   // Enqueue k sweeps a.s -> a.s_new as one resident launch (fill: device flag, nullable);
@@ -565,7 +565,7 @@ struct Solver {
   template <typename T>
   int chunk(T *buf0, T *buf1, int &cur, int k, bool dc, Faces<T> w, double out[NV]) {
     bool ran = false;
-    if (sizeof(T) == 8 && resident<T>()) {
+    if (sizeof(T) == 8 && resident<T>(k)) {
       T *buf[2] = {buf0, buf1};
       SweepArgs<T> a = sweep_args<T>(buf[cur], buf[cur ^ 1], dc, c->partial);
       a.w = w;
@@ -684,7 +684,6 @@ struct Solver {
     double ri_prev = 0;
     int ng = 2;                          // chunks in the next group
     int cd = 0;                          // buffer holding the correction
-    bool whole = resident<float>();             // a chunk is one resident launch
     for (;;) {
       int ks[G], from[G];
       int nch = 0;
@@ -693,7 +692,7 @@ struct Solver {
         const int k = (int)std::min<long long>(K, budget - enq);
         from[nch] = cd;
         long long nb;
-        if (whole) {
+        if (resident<float>(k)) {
           HIPCHK(hipEventRecord(c->evp[4 * nch], c->st));
           SweepArgs<float> a = sweep_args<float>(c->s32[cd], c->s32[cd ^ 1], true, c->partial);
           a.w = faces32(c);
@@ -746,7 +745,6 @@ struct Solver {
         int g = 0;
         while (it < h.it) it += ks[g++];
         cd = from[g];
-        whole = false;
         c->res.C = 0;
         h.state = CTL_RUN;
         h.lost = 0;
@@ -1432,7 +1430,7 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
     T *b[2] = {b0, b1};
     long long nb = S.nblk;
     int j = 0;
-    if (S.resident<T>()) {
+    if (S.resident<T>(k)) {
       SweepArgs<T> a = S.sweep_args<T>(b[cc], b[cc ^ 1], dc, c->partial);
       a.w = w;
       a.gscale = (T)gs;
@@ -1575,7 +1573,7 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
     while (S.it < p->max_iter) {
       const long k = std::min<long>(K, p->max_iter - S.it);
       bool ran = false;
-      if (whole && c->resn.C) {
+      if (whole && c->resn.C && k >= RESIDENT_LEAST_NERNST) {
         SweepArgs<double> w = S.sweep_args<double>(c->s64[cur], c->s64[cur ^ 1], false, c->partial);
         w.w = faces64(c);
         double *half[2] = {eta, eta + n};

@@ -394,6 +394,12 @@ void launch_fill_gated(float *a, float *b, long long n, const SolveCtl *ctl, hip
 constexpr int RESIDENT_LANES = 512;            // lanes (columns) per workgroup
 constexpr int RESIDENT_LDS = 156 * 1024;       // most LDS a sub-box may take
 constexpr int RESIDENT_LDS_ALONE = 84 * 1024;  // more than half a CU's: one workgroup per CU
+// Fewest sweeps of a resident launch: it reads the coefficients and fills the chip's registers once,
+// which takes as long as a few sweeps of the other launches.  Launches of k sweeps against those, in
+// time: FP32 forward / transpose on 175x89x89 k = 2 0.92 / 0.82, 4 1.05 / 0.96, 6 1.16 / 1.09, on
+// 256x120x118 (lean columns) 4 0.94 / 0.85, 6 1.09 / 1.01; FP64 transpose on 128x64x64 4 0.93, 6 1.02;
+// Nernst there 6 0.96, 8 1.02.  (A box of 64x32x32 gains from 2 sweeps on in FP32.)
+constexpr int RESIDENT_LEAST = 6, RESIDENT_LEAST_NERNST = 8;
 struct ResidentPlan {
   int C;                // cells per lane along z; 0: the box does not fit
   int X, Y;             // columns of a sub-box

@@ -255,3 +255,27 @@ def test_given_up_launches_of_one_kind_leave_the_others(sv):
         sv.set_wait_limit(pb.ctx, limit)
         for k, (a, b) in enumerate(zip(kinds(pb.ctx), want)):
             assert (a - b).abs().max() <= 1e-12 * max(1.0, float(b.abs().max())), (limit, k)
+
+
+@pytest.mark.parametrize("shape", [(64, 32, 33), (175, 89, 89)])
+@pytest.mark.parametrize("check", [2, 4, 6, 8])
+def test_chunks_around_the_fewest_sweeps_of_a_resident_launch(sv, shape, check):
+    # chunks below and above it, and solves whose last chunk is shorter than the others: FP32 states
+    # equal bit for bit, FP64 and Nernst ones to their rounding
+    inputs = inputs_of(shape)
+    for sweeps in (3 * check, 2 * check + 2):
+        kw = dict(tol=0.0, max_iter=sweeps, check_every=check)
+        pb, res = problem(sv, inputs), []
+        p64, pn = sv.params(precision="fp64", **kw, **FINITE), sv.params(
+            s_in=0.2, s_eq=0.7, Da=5.0, mode=0, **kw)
+        runs = both(sv, problem(sv, inputs), **kw, **FINITE)
+        for a, b in zip(runs[:2], runs[2:]):
+            assert a[1].iterations == b[1].iterations == sweeps
+            assert torch.equal(a[0], b[0])
+        for _ in range(2):
+            res.append([sv.solve_soc_steady(pb.ctx, p64)[0],
+                        sv.solve_soc_adjoint(pb.ctx, p64, want_psi=True)[2],
+                        sv.solve_nernst(pb.ctx, pn, omega=0.3)[0]])
+            sv.set_tiles(pb.ctx, 0, 0, 0, 1)
+        for a, b in zip(*res):
+            assert (a - b).abs().max() <= 1e-12 * max(1.0, float(b.abs().max()))
