@@ -2005,7 +2005,9 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       }
       return zbest;
     };
-    int zc2 = pick_zc2(std::vector<int>(n, 1));
+    std::vector<int> act(n, 0);
+    for (int i = 0; i < n; ++i) act[i] = !done[i];
+    int zc2 = pick_zc2(act);
     auto build = [&](int ty, int zc, std::vector<BatchProb> &hp, std::vector<int> &tp) {
       hp.assign(n, BatchProb{});
       tp.clear();
@@ -2195,7 +2197,6 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       for (int g = 0; g < replays; ++g) HIPCHK(hipGraphLaunch(exec, bs));
       HIPCHK(hipMemcpyAsync(h_ctl, d_ctl, sizeof(SolveCtl) * n, hipMemcpyDeviceToHost, bs));
       HIPCHK(hipStreamSynchronize(bs));
-      std::vector<int> act(n, 0);
       nact = 0;
       for (int i = 0; i < n; ++i) {
         if (h_ctl[i].state == CTL_DIVERGED)

@@ -131,3 +131,34 @@ def test_batch48_design_sweep(sv, orc):
     torch.cuda.synchronize()
     seq = time.time() - t
     print(f"one after another {seq:.2f}s; batched/sequential {makespan / seq:.2f}", flush=True)
+
+
+BIG = [(160, 64, 60), (96, 48, 48)]            # with the boxes of small_batch: a few tiles each
+
+
+@pytest.mark.parametrize("tiled", ["all", "one", "small", "big"])
+def test_tiled_and_resident_problems_in_one_batch(sv, tiled):
+    # contexts whose shapes were set are swept in the tiled launches (two sweeps each, work lists
+    # that shrink as problems finish, the polish by marches); the others in resident launches.
+    # Both do the arithmetic of the single solves: the same sweeps, the same states to the
+    # polish's rounding
+    probs = small_batch(5, 900)
+    for k, shape in enumerate(BIG):
+        g = I.fibres_nonoverlap(*shape, 3.0, 0.85, 910 + k)
+        probs.append({"solid": g.solid, "velocity": I.darcy_velocity(g.solid, 1.0, device="cuda")})
+    n = len(probs)
+    chosen = {"all": range(n), "one": [2], "small": range(n - 2), "big": [n - 2, n - 1]}[tiled]
+    pbs = [sv.Problem.create(p["solid"], *p["velocity"]) for p in probs]
+    alone = [sv.Problem.create(p["solid"], *p["velocity"]) for p in probs]
+    for k in chosen:
+        sv.set_tiles(pbs[k].ctx, 0, 0, 0, 1)
+    lengths = [dict(), dict(polish_iters=50), dict(), dict(polish_iters=150), dict(), dict(), dict()]
+    params = [sv.params(precision="fp32", tol=(1e-8 if k % 2 else 1e-9), check_every=200, **kw)
+              for k, kw in enumerate(lengths)]
+    params[4].max_iter = 400                     # stops short
+    states, stats = sv.batch_solve([pb.ctx for pb in pbs], params)
+    for k in range(n):
+        s, st = sv.solve_soc_steady(alone[k].ctx, params[k])
+        assert stats[k].status == st.status == (sv.NOT_CONVERGED if k == 4 else sv.OK), k
+        assert stats[k].iterations == st.iterations and stats[k].cycles == st.cycles, k
+        assert (states[k] - s).abs().max() <= 1e-12, k
