@@ -157,6 +157,8 @@ struct socfv_ctx {
   // next tag
   ResidentPlan res{}, res64{}, resn{};   // (resn: the Nernst iteration's)
   bool res_planned = false;
+  std::vector<ResidentPlan> batch_plans[2];   // resident_plans in FP32, FP64 (made at first use:
+  bool batch_planned[2] = {false, false};     // up to 0.1 ms)
   unsigned long long *inbox = nullptr;
   void *res_diag = nullptr;
   long long inbox_words = 0;
@@ -934,6 +936,40 @@ void choose_resident(const std::vector<int> &order, const std::vector<std::vecto
   }
 }
 
+// The splits of a problem's box in a batch (none where its shapes were set).
+std::vector<ResidentPlan> batch_plans(socfv_ctx *c, int bytes) {
+  const int k = bytes == 8;
+  if (c->tiles_fixed || !two_path(c->g)) return {};
+  if (!c->batch_planned[k]) c->batch_plans[k] = resident_plans(c->g, bytes, c->ncu);
+  c->batch_planned[k] = true;
+  return c->batch_plans[k];
+}
+
+// Modelled time per sweep of resident launches over the problems of `order`, in chunks of K sweeps
+// (their launches, the read of the states and the refreshes: 40 us a chunk on 64x32x32, 90 on
+// 160x96x96).
+double resident_time(std::vector<int> order, const std::vector<std::vector<ResidentPlan>> &plans,
+                     socfv_ctx *const *ctxs, int ncu, int K) {
+  double total = 0;
+  while (!order.empty()) {
+    std::vector<int> set;
+    std::vector<const ResidentPlan *> pick;
+    choose_resident(order, plans, ctxs, ncu, set, pick);
+    double us = 0, words = 0;
+    for (const ResidentPlan *q : pick) {
+      us = std::max(us, q->us - q->words_us);
+      words += q->words_us;
+    }
+    total += us + words + 90.0 / K;
+    for (int i : set) order.erase(std::find(order.begin(), order.end(), i));
+  }
+  return total;
+}
+
+// Cells per us that the tiled launches sweep: boxes of 4 to 8 million cells, alone and with smaller
+// ones, 212 to 232 thousand.
+constexpr double TILED_RATE = 220e3;
+
 // The resident part of a batched solve: every problem that fits the chip, several at a time, one
 // launch per chunk of K sweeps.  Which problems share a launch, and how many workgroups each gets,
 // is chosen anew after every read of the states (choose_resident), those with the most sweeps left
@@ -945,13 +981,25 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
                    BatchResident &br, hipStream_t bs) {
   const int ncu = ctxs[0]->ncu;
   std::vector<std::vector<ResidentPlan>> plans(n);
-  bool any = false;
-  for (int i = 0; i < n; ++i)
-    if (h_ctl[i].state == CTL_RUN && two_path(ctxs[i]->g) && !ctxs[i]->tiles_fixed) {
-      plans[i] = resident_plans(ctxs[i]->g, 4, ncu);
-      any = any || !plans[i].empty();
+  std::vector<int> fit;
+  bool others = false;
+  double cells = 0;
+  for (int i = 0; i < n; ++i) {
+    if (h_ctl[i].state != CTL_RUN) continue;
+    plans[i] = batch_plans(ctxs[i], 4);
+    if (plans[i].empty()) {
+      others = true;
+    } else {
+      fit.push_back(i);
+      cells += (double)ctxs[i]->g.n;
     }
-  if (!any) return 0;
+  }
+  if (fit.empty()) return 0;
+  // Beside problems that run in tiled launches anyway, small ones cost those little: 64x32x32 beside
+  // 300x160x128 0.2 us a sweep (1.3 resident, and its launches: 800 sweeps 21.4 ms against 22.8),
+  // where 160x96x96 costs 8.5 us and resident 2.3 (27.9 against 23.9).  Resident where the model
+  // gains a fifth of that cost (96x78x78, where it does not: 23.7 ms resident, 23.3 tiled).
+  if (others && resident_time(fit, plans, ctxs, ncu, K) > 0.8 * cells / TILED_RATE) return 0;
   {
     long long items = 0;
     for (int i = 0; i < n; ++i) items += march64_blocks(ctxs[i]->g);
@@ -2260,8 +2308,8 @@ int socfv_batch_solve(int n, socfv_ctx *const *ctxs, const socfv_params *p,
       std::vector<std::vector<ResidentPlan>> plans(n);
       std::vector<int> order;
       for (int i = 0; i < n; ++i)
-        if (nk[i] > 0 && two_path(ctxs[i]->g) && !ctxs[i]->tiles_fixed) {
-          plans[i] = resident_plans(ctxs[i]->g, 8, ncu);
+        if (nk[i] > 0) {
+          plans[i] = batch_plans(ctxs[i], 8);
           if (!plans[i].empty()) order.push_back(i);
         }
       HIPCHK(hipEventRecord(ctxs[0]->t0, bs));

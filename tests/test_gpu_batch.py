@@ -136,7 +136,7 @@ def test_batch48_design_sweep(sv, orc):
 BIG = [(160, 64, 60), (96, 48, 48)]            # with the boxes of small_batch: a few tiles each
 
 
-@pytest.mark.parametrize("tiled", ["all", "one", "small", "big"])
+@pytest.mark.parametrize("tiled", ["all", "one", "small", "big", "all but one"])
 def test_tiled_and_resident_problems_in_one_batch(sv, tiled):
     # contexts whose shapes were set are swept in the tiled launches (two sweeps each, work lists
     # that shrink as problems finish, the polish by marches); the others in resident launches.
@@ -147,7 +147,8 @@ def test_tiled_and_resident_problems_in_one_batch(sv, tiled):
         g = I.fibres_nonoverlap(*shape, 3.0, 0.85, 910 + k)
         probs.append({"solid": g.solid, "velocity": I.darcy_velocity(g.solid, 1.0, device="cuda")})
     n = len(probs)
-    chosen = {"all": range(n), "one": [2], "small": range(n - 2), "big": [n - 2, n - 1]}[tiled]
+    chosen = {"all": range(n), "one": [2], "small": range(n - 2), "big": [n - 2, n - 1],
+              "all but one": range(1, n)}[tiled]   # (the one goes along with them)
     pbs = [sv.Problem.create(p["solid"], *p["velocity"]) for p in probs]
     alone = [sv.Problem.create(p["solid"], *p["velocity"]) for p in probs]
     for k in chosen:
