@@ -2621,8 +2621,14 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
           for (int j = j0; j < std::min(m, j0 + guess); ++j) launch_flow_cg_iter(a, j, m, c->st);
           launch_flow_project(a, m, c->st);
         }
+        // one read for the group and, where the check follows it, the change of the last step (its
+        // place in hres is used only when every step ran)
+        if (s + grp == k) launch_reduce(a.pdu, 3 * a.nbf, 2, 0u, c->dres, c->st);
         HIPCHK(hipGetLastError());
         HIPCHK(hipMemcpyAsync(c->hres, a.sc, sizeof(double) * FS_N, hipMemcpyDeviceToHost, c->st));
+        if (s + grp == k)
+          HIPCHK(hipMemcpyAsync(c->hres + FS_N, c->dres, sizeof(double) * 2,
+                                hipMemcpyDeviceToHost, c->st));
         HIPCHK(hipStreamSynchronize(c->st));
         const long ran = (long)c->hres[FS_STEPS] - steps - s;
         s += ran;
@@ -2645,16 +2651,10 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
         }
         seen = c->hres[FS_CG_TOTAL];
       }
-      launch_reduce(a.pdu, 3 * a.nbf, 2, 0u, c->dres, c->st);
-      HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpyAsync(c->hres, c->dres, sizeof(double) * 2, hipMemcpyDeviceToHost, c->st));
-      HIPCHK(hipMemcpyAsync(c->hres + 2, a.sc + FS_CG_TOTAL, sizeof(double),
-                            hipMemcpyDeviceToHost, c->st));
-      HIPCHK(hipStreamSynchronize(c->st));
       steps += k;
-      du = std::sqrt(c->hres[0]);
-      un = std::sqrt(c->hres[1]);
-      const double total = c->hres[2];
+      du = std::sqrt(c->hres[FS_N]);
+      un = std::sqrt(c->hres[FS_N + 1]);
+      const double total = seen;
       if (!std::isfinite(du) || !std::isfinite(un))
         return fail(SOCFV_DIVERGED, "flow steps diverged at step %ld", steps);
       // cap of this phase's CG: twice the recent average plus 4, at least 8

@@ -225,3 +225,18 @@ def test_a_given_up_cg_leaves_no_trace(sv, shape):
             for a, b in zip(got[:4], want[:4]):
                 assert torch.equal(a, b), (cap, k)
         start = want[:4]
+
+
+@pytest.mark.parametrize("shape", [(32, 16, 16), (130, 36, 36)])      # one launch / separate kernels
+@pytest.mark.parametrize("check", [1, 3])
+def test_the_change_is_that_of_the_last_step(sv, shape, check):
+    # 12 steps and the first 11 of them (checked at the same steps; with one at the end that ends
+    # there) differ by the last step, whose relative change the call reports
+    g = I.fibres_nonoverlap(*shape, 2.5, 0.85, 5)
+    ctx = sv.setup_geometry(torch.as_tensor(g.solid, device="cuda"))
+    runs = [sv.solve_stokes(ctx, cfl=3.0, max_steps=n, check_every=check, tol=0.0, cg_max=64)
+            for n in (11, 12)]
+    assert [r[4].steps for r in runs] == [11, 12]
+    du = sum(float(((a - b) ** 2).sum()) for a, b in zip(runs[1][:3], runs[0][:3])) ** 0.5
+    un = sum(float((a ** 2).sum()) for a in runs[1][:3]) ** 0.5
+    assert abs(runs[1][4].change - du / un) <= 1e-9 * du / un
