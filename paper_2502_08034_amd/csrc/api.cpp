@@ -357,17 +357,18 @@ int unconnected_on_host(socfv_ctx *c, long long *missing) {
   return 0;
 }
 
-// The same on the GPU.  The labels take the buffer that a solve's FP32 state will use.
+// The same on the GPU.  The labels take the buffer of the x velocities, which a context for solves
+// needs next; the flow step, which needs none, gives it back.
 int unconnected(socfv_ctx *c, long long *missing) {
   const long long n = c->g.n;
   if (n >= (1ll << 31) - 1) return unconnected_on_host(c, missing);
-  if (!c->s32[0] && hipMalloc(&c->s32[0], sizeof(int) * (size_t)(n + 1)) != hipSuccess) {
+  if (hipMalloc(&c->w32[0], sizeof(int) * (size_t)(n + 1)) != hipSuccess) {
     (void)hipGetLastError();               // no room: the host's memory serves
-    c->s32[0] = nullptr;
+    c->w32[0] = nullptr;
     return unconnected_on_host(c, missing);
   }
   const int nb = flags_blocks(c->g);
-  launch_connect(c->g, c->flags, (int *)c->s32[0], c->partial, nb, c->st);
+  launch_connect(c->g, c->flags, (int *)c->w32[0], c->partial, nb, c->st);
   HIPCHK(hipGetLastError());
   double cnt = 0;
   TRY(reduce_to_host(c, nb, 1, 0u, &cnt));
@@ -2513,6 +2514,10 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
   const long long nf[3] = {(long long)(g.nx + 1) * g.ny * g.nz,
                            (long long)g.nx * (g.ny + 1) * g.nz,
                            (long long)g.nx * g.ny * (g.nz + 1)};
+  if (c->w32[0] && !c->w32[1]) {         // (the labels of setup: no velocity was set)
+    hfree(c->w32[0]);
+    c->w32[0] = nullptr;
+  }
   FlowArgs a{};
   a.g = g;
   a.flags = c->flags;

@@ -60,3 +60,36 @@ def test_winding_channel(sv, cut):
     want = expected(solid)
     assert (want > 0) == cut
     assert unconnected(sv, solid) == want
+
+
+def test_the_labels_take_no_memory_of_their_own(sv):
+    # a context holds 1 B a cell of flags, and with a velocity 36 B of faces; the 4 B a cell of the
+    # labels are the x faces' (or given back by the flow step), so no sum has them on top
+    nx, ny, nz = 256, 256, 192
+    n, slack = nx * ny * nz, 16 << 20
+    solid = torch.zeros((nz, ny, nx), dtype=torch.uint8, device="cuda")
+    u = [torch.zeros(s, dtype=torch.float64, device="cuda")
+         for s in ((nz, ny, nx + 1), (nz, ny + 1, nx), (nz + 1, ny, nx))]
+    u[0].fill_(1.0)
+    torch.cuda.synchronize()
+
+    def held(ctx_of):
+        before = torch.cuda.mem_get_info()[0]
+        ctx = ctx_of()
+        torch.cuda.synchronize()
+        used = before - torch.cuda.mem_get_info()[0]
+        del ctx
+        return used
+
+    def with_velocity():
+        ctx = sv.setup_geometry(solid)
+        sv.set_velocity(ctx, *u)
+        return ctx
+
+    def after_flow():
+        ctx = sv.setup_geometry(solid)
+        sv.solve_stokes(ctx, start=[*u, None], max_steps=1, cg_max=1, tol=0.0)
+        return ctx
+
+    assert held(with_velocity) <= 37 * n + slack
+    assert held(after_flow) <= n + slack
