@@ -857,7 +857,7 @@ struct BatchResident {
   unsigned tag = 1;
   bool ready = false;
 
-  // false: no room
+  // false: no room (and nothing is held)
   bool make(int n, int ncu, long long refresh_items, hipStream_t st) {
     words = 2 * RESIDENT_BLOCK_WORDS * ncu;
     ready = hipMalloc(&tab, sizeof(*tab) * 2 * n) == hipSuccess &&
@@ -868,9 +868,14 @@ struct BatchResident {
             hipMalloc(&part, sizeof(double) * NV * ncu) == hipSuccess &&
             hipMalloc(&refresh, sizeof(*refresh) * 2 * n) == hipSuccess &&
             hipMalloc(&refresh_of, sizeof(int) * refresh_items) == hipSuccess;
-    if (ready) launch_fill_f64((double *)inbox, words, 0.0, st);
-    else (void)hipGetLastError();
-    return ready;
+    if (ready) {
+      launch_fill_f64((double *)inbox, words, 0.0, st);
+      return true;
+    }
+    (void)hipGetLastError();
+    release();
+    *this = BatchResident{};
+    return false;
   }
   // the first of k tags
   unsigned take(int k, hipStream_t st) {
