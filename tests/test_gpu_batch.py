@@ -163,3 +163,24 @@ def test_tiled_and_resident_problems_in_one_batch(sv, tiled):
         assert stats[k].status == st.status == (sv.NOT_CONVERGED if k == 4 else sv.OK), k
         assert stats[k].iterations == st.iterations and stats[k].cycles == st.cycles, k
         assert (states[k] - s).abs().max() <= 1e-12, k
+
+
+@pytest.mark.parametrize("mode", ["finite", "pinned"])
+def test_single_and_two_sweep_items_in_one_batch(sv, orc, mode):
+    # tiled launches with both work lists: problems swept one sweep a launch and two a launch (one of
+    # them a small box that fits the chip and goes along)
+    probs = small_batch(6, 950)
+    kw = dict(s_in=1.0, s_eq=0.0, Da=0.45, mode=0) if mode == "finite" else \
+        dict(s_in=0.0, s_eq=1.0, Da=0.0, mode=1)
+    pbs = [sv.Problem.create(p["solid"], *p["velocity"]) for p in probs]
+    for k in range(5):
+        sv.set_tiles(pbs[k].ctx, 0, 0, 0, k % 2)
+    params = [sv.params(precision="fp32", tol=1e-9, check_every=100, **kw) for _ in probs]
+    states, stats = sv.batch_solve([pb.ctx for pb in pbs], params)
+    for p, s, st in zip(probs, states, stats):
+        assert st.status == sv.OK
+        op = orc.Problem(p["solid"], *p["velocity"], s_in=kw["s_in"], s_eq=kw["s_eq"],
+                         Da=kw["Da"], pinned=bool(kw["mode"]))
+        assert orc.residual_norm(op, s.cpu().numpy()) < 1.5e-9
+        o = orc.outputs(op, s.cpu().numpy())
+        assert abs(o["U"] - st.U) <= 1e-12 * max(1.0, abs(st.U))

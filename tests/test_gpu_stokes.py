@@ -240,3 +240,23 @@ def test_the_change_is_that_of_the_last_step(sv, shape, check):
     du = sum(float(((a - b) ** 2).sum()) for a, b in zip(runs[1][:3], runs[0][:3])) ** 0.5
     un = sum(float((a ** 2).sum()) for a in runs[1][:3]) ** 0.5
     assert abs(runs[1][4].change - du / un) <= 1e-9 * du / un
+
+
+@pytest.mark.parametrize("cap", [1, 15, 16, 17, 31, 90])
+def test_stalled_steps_of_the_separate_kernels_equal_the_single_launch(sv, cap):
+    # a target that no CG reaches: every step runs to the cap, which the separate kernels (wait
+    # limit 0) reach in one go or after one or several stalls (first guess 16), or with the last
+    # iteration of a group (whose second half then makes the last update of p)
+    g = I.fibres_nonoverlap(48, 32, 32, 2.5, 0.85, 3)
+    solid = torch.as_tensor(g.solid, device="cuda")
+    runs = []
+    for limit in (1.0, 0.0):
+        ctx = sv.setup_geometry(solid)
+        sv.set_wait_limit(ctx, limit)
+        runs.append(sv.solve_stokes(ctx, cfl=2.0, max_steps=11, check_every=4, cg_theta=1e-200,
+                                    cg_max=cap, tol=0.0, want_pressure=True))
+    a, b = runs
+    assert a[4].steps == b[4].steps == 11
+    assert 0 < a[4].cg_iterations == b[4].cg_iterations <= 11 * cap
+    for x, y in zip(a[:4], b[:4]):
+        assert torch.equal(x, y)
