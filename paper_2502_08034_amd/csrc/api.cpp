@@ -1608,7 +1608,8 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
     Solver S{c, &pt};
     TRY(S.setup());
     TRY(ensure_resident(c));
-    const bool whole = c->resn.C > 0 && c->inbox && !c->tiles_fixed;
+    const bool whole = c->resn.C > 0 && c->inbox && !c->tiles_fixed &&
+                       std::min<long>(S.chunk_len(), p->max_iter) >= RESIDENT_LEAST_NERNST;
     // the overpotentials; the resident iteration reads one half and writes the other
     HIPCHK(hipMalloc(&eta, sizeof(double) * (size_t)n * (whole ? 2 : 1)));
     launch_fill_f64(eta, whole ? 2 * n : n, 0.0, c->st);
