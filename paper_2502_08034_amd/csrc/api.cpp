@@ -1833,8 +1833,6 @@ int socfv_autotune(socfv_ctx *c, int sweeps, int best[3], void *hip_stream) {
       if (ms < best_ms) { best_ms = ms; best_t = t; }
     }
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
   // two-sweep kernel: z chunk
   float best2 = 1e30f;
   int best_zc2 = c->tiles.zc2;
@@ -1863,6 +1861,8 @@ int socfv_autotune(socfv_ctx *c, int sweeps, int best[3], void *hip_stream) {
       if (ms < best2) { best2 = ms; best_zc2 = zc2; }
     }
   }
+  (void)hipEventDestroy(e0);
+  (void)hipEventDestroy(e1);
   best_t.zc2 = best_zc2;
   best_t.two = c->tiles.two;
   c->tiles = best_t;

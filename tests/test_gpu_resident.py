@@ -279,3 +279,17 @@ def test_chunks_around_the_fewest_sweeps_of_a_resident_launch(sv, shape, check):
             sv.set_tiles(pb.ctx, 0, 0, 0, 1)
         for a, b in zip(*res):
             assert (a - b).abs().max() <= 1e-12 * max(1.0, float(b.abs().max()))
+
+
+@pytest.mark.parametrize("shape", [(96, 48, 40), (258, 128, 130)])     # fits the chip / does not
+def test_autotune_leaves_the_results(sv, shape):
+    # it times shapes of the launches that boxes beyond the chip take and keeps the fastest; a
+    # box that fits goes on with its resident launches
+    pb = problem(sv, inputs_of(shape))
+    p = sv.params(precision="fp32", tol=0.0, max_iter=80, check_every=40, **FINITE)
+    s, st = sv.solve_soc_steady(pb.ctx, p)
+    ty, zc, zc2 = sv.autotune(pb.ctx, 4)
+    assert ty in (1, 2, 4, 8, 16) and 1 <= zc <= 64 and 1 <= zc2 <= 128
+    t, tt = sv.solve_soc_steady(pb.ctx, p)
+    assert tt.iterations == st.iterations == 80 and (tt.tile_y, tt.z_chunk) == (ty, zc)
+    assert torch.equal(s, t)
