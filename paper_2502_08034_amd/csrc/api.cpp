@@ -2599,16 +2599,16 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     int guess = 16, from = -1;           // CG iterations to enqueue; where a stalled CG goes on
     double seen = 0.0;
     unsigned tag = 1;                    // of the whole CG's words
-    long group = 1;                      // steps to enqueue
-    const long most = n > (1 << 19) ? 1 : 4;   // (a large box's step hides the read)
     int status = SOCFV_NOT_CONVERGED;
     while (steps < p->max_steps) {
       const long k = std::min<long>(p->check_every, p->max_steps - steps);
-      // The steps are enqueued a few at a time with as many CG iterations each as the last ones
-      // took and some more (a launch past a CG's end returns at once but costs about 2 us); a
-      // step that needs more stalls what follows, and the read after the group resumes it.
+      // A step is enqueued with as many CG iterations as the last one took and some more (a launch
+      // past a CG's end returns at once but costs about 2 us); one that needs more is resumed after
+      // the read behind it.  Up to four steps between reads were slower, the iterations being
+      // guessed from older steps: 200 steps on 66x45x45 38.3 ms against 35.9, on 96x64x64 76.7
+      // against 73.7, on 256x128x128 370 against 364.  Steps of one launch need no guess.
       for (long s = 0; s < k;) {
-        const long grp = std::min<long>(k - s, whole ? 64 : group);
+        const long grp = whole ? std::min<long>(k - s, 64) : 1;
         for (long q = 0; whole && q < grp; ++q) {
           if (tag > 0xffffffffu - (2u * m + 2u)) {
             launch_fill_f64((double *)a.words, CGW_WORDS, 0.0, c->st);
@@ -2623,16 +2623,16 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
           launch_flow_project(a, m, c->st);
           tag += 2u * m + 2u;
         }
-        for (long q = 0; !whole && q < grp; ++q) {
-          if (q > 0 || from < 0) {
+        if (!whole) {
+          if (from < 0) {
             launch_flow_predict(a, c->st);
             launch_flow_cg_init(a, c->st);
           }
-          const int j0 = q == 0 && from > 0 ? from : 0;
+          const int j0 = std::max(from, 0);
           for (int j = j0; j < std::min(m, j0 + guess); ++j) launch_flow_cg_iter(a, j, m, c->st);
           launch_flow_project(a, m, c->st);
         }
-        // one read for the group and, where the check follows it, the change of the last step (its
+        // one read for these steps and, where the check follows it, the change of the last step (its
         // place in hres is used only when every step ran)
         if (s + grp == k) launch_reduce(a.pdu, 3 * a.nbf, 2, 0u, c->dres, c->st);
         HIPCHK(hipGetLastError());
@@ -2652,13 +2652,10 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
         } else if (c->hres[FS_STALL] != 0.0) {
           from = (int)c->hres[FS_CG_STEP];
           guess = std::max(8, from / 2);
-          group = 1;
           launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
         } else if (!whole) {
           from = -1;
-          const int next = (int)std::ceil(1.2 * (c->hres[FS_CG_TOTAL] - seen) / (double)ran) + 3;
-          group = 2 * next < guess ? 1 : std::min(2 * group, most);   // a step of many: alone
-          guess = next;
+          guess = (int)std::ceil(1.2 * (c->hres[FS_CG_TOTAL] - seen)) + 3;
         }
         seen = c->hres[FS_CG_TOTAL];
       }
