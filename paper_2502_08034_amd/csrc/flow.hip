@@ -486,9 +486,7 @@ __global__ void __launch_bounds__(FB) k_flow_cg_b(FlowArgs a, int j, bool last) 
 // which a lane advances itself (d = z + beta d from the neighbour's z); what travels between
 // workgroups is z, and the logical blocks' partials, as tagged words that every workgroup sums in
 // the order of the separate kernels.  An iteration then costs its two exchanges instead of two
-// launches and, per step, launches past the end: 100 steps from rest on 48 x 32 x 32 take 8.9 ms
-// against 17 (60 on 64 x 45 x 45 17.7 against 19.1, which is why larger boxes keep the separate
-// kernels), with the same arithmetic cell by cell and sum by sum.  A word is written again only
+// launches and, per step, launches past the end (both sides measured at CGW_CELLS), with the same arithmetic cell by cell and sum by sum.  A word is written again only
 // after a sum that its readers have contributed to since they read it, so one slot per word is
 // enough: z and the residual's sums after d.q's, d.q's after the residual's (which therefore
 // have words of their own).  Waits

@@ -233,7 +233,13 @@ void launch_flow_cg_init(const FlowArgs &a, hipStream_t st);
 void launch_flow_cg_iter(const FlowArgs &a, int j, int cap, hipStream_t st);
 // a step's CG (cg_init included) in one launch of up to m iterations, from the pressure p to the
 // pressure q; 2 m + 2 tags from tag0
-constexpr long long CGW_CELLS = 1ll << 17;       // largest box
+// Largest box, 208 workgroups.  Its sums go from every workgroup to every other one, so an
+// iteration grows with their number; 100 steps, one launch against the separate kernels (later ones
+// / from rest): 40x32x32 9.1 / 9.4 ms against 18.4 / 19.0, 56x38x38 13.6 / 15.6 against 19.6 / 21.6,
+// 60x42x42 (207 workgroups) 22.9 / 20.1 against 25.0 / 22.6, 62x42x42 (214) 34.2 / 23.2 against
+// 33.8 / 23.6, 118x32x31 (229) 80.9 / 36.3 against 70.3 / 33.3, 64x45x45 29.0 / 25.6 against
+// 23.7 / 22.6.
+constexpr long long CGW_CELLS = 208 * 512;
 constexpr int CGW_BLOCKS = 512;                  // its logical blocks
 constexpr int CGW_SUMS = 4;                      // r.z, r.r, the floor's, d.q
 constexpr long long CGW_WORDS = 2 * CGW_CELLS + 2ll * CGW_SUMS * CGW_BLOCKS * (CGW_BLOCKS / 2);
