@@ -219,7 +219,8 @@ int socfv_solve_soc_adjoint(socfv_ctx *c, const socfv_params *p, double *dU_dkap
  * problems finish), and so does the FP64 polish.  For the others each FP32 sweep is one launch
  * over a tile work list spanning them (persistent blocks taking tiles from a
  * device counter), and each problem keeps its own dt, tau, FP64 refreshes and stopping rule
- * (its own p[i]), all decided on the device: one chunk of check_every sweeps (rounded up to
+ * (its own p[i]), all decided on the device; small boxes beside ones that do not fit go along with
+ * those where that takes less time.  One chunk of check_every sweeps (rounded up to
  * a multiple of 4) with the work lists, the per-problem residuals and decisions and the
  * refreshes is captured once as a hipGraph and replayed, the host reading the problems'
  * states every few chunks to re-tile the remaining ones; the single-sweep block shape is
@@ -337,24 +338,32 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
  * with two_sweeps set (the default), FP32 sweeps run two sweeps per launch on blocks of 1024
  * lanes marching z_chunk2 cells: rows of 64 lanes (16 rows) or, where that wastes fewer lanes
  * on the box, rows of 32 lanes (32 rows), two cells per lane for even nx and one for odd.
- * FP32 correction sweeps of a box that fits the chip's registers (about 4 million cells) run a
- * whole chunk per launch instead, one workgroup per CU exchanging sub-box faces with its
- * neighbours (the same arithmetic cell by cell); a context whose shapes were set by
- * socfv_set_tiles runs the launches asked for.
+ * Boxes that fit the chip's registers run a whole chunk of sweeps per launch instead (FP32
+ * corrections, FP64 sweeps, Nernst iterations; the same arithmetic cell by cell), one workgroup
+ * per CU exchanging sub-box faces with its neighbours.  A box fits if it splits into at most as
+ * many sub-boxes of up to 512 columns of up to 32 cells (16 in FP64, 8 for Nernst) along z as
+ * there are CUs: at most 4,194,304 cells in FP32 on 256 CUs (2,097,152 in FP64, 1,048,576 for
+ * Nernst) and fewer where the sides do not divide so (256 x 128 x 128 fits, 257 x 128 x 128 and
+ * 256 x 130 x 120 do not).  Chunks of fewer than 6 sweeps (8 Nernst iterations) take the other
+ * launches, and so does a context whose shapes were set by socfv_set_tiles.
  * socfv_set_tiles overrides them for a context (0 = keep; two_sweeps: -1 keep, 0 off, 1 on
  * with the row width chosen for the box, 2 on with 64-lane rows, 3 on with 32-lane rows; a
  * new row width re-picks z_chunk2 unless given); socfv_autotune times candidate shapes on
- * this context's problem (`sweeps` sweeps each) and keeps the fastest; best[3] (host,
- * nullable) receives tile_y, z_chunk, z_chunk2.
+ * this context's problem (`sweeps` sweeps each) and keeps the fastest for these launches (a box
+ * that fits the chip goes on with its chunks in one launch); best[3] (host, nullable) receives
+ * tile_y, z_chunk, z_chunk2.
  */
 int socfv_set_tiles(socfv_ctx *c, int tile_y, int z_chunk, int z_chunk2, int two_sweeps);
 int socfv_autotune(socfv_ctx *c, int sweeps, int best[3], void *hip_stream);
 
 /*
- * Longest time (s, default 1) that a workgroup of a resident launch waits for its neighbours.
- * They run together on an otherwise idle GPU; where other work holds CUs for longer, the launch
- * is given up, its input is intact, and the solve goes on with two-sweep launches (from then on
- * for this context).  0 gives up at the first value that is not there yet.
+ * Longest time (s, default 1, at most 3600) that a workgroup of a launch whose workgroups wait for
+ * each other does wait: chunks of sweeps or Nernst iterations in one launch, batched ones, and the
+ * flow step's single-launch CG.  They run together on an otherwise idle GPU; where other work holds
+ * CUs for longer, the launch is given up, its input is intact, and the call goes on with the other
+ * launches: single solves in that precision (or Nernst iterations) from then on for this context, a
+ * batch and a flow step for the rest of the call.  A given-up launch shows in no result and in no
+ * statistic but the time.  0 gives up at the first value that is not there yet.
  */
 int socfv_set_wait_limit(socfv_ctx *c, double seconds);
 
