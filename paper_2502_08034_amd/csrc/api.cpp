@@ -1006,121 +1006,119 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
   // where 160x96x96 costs 8.5 us and resident 2.3 (27.9 against 23.9).  Resident where the model
   // gains a fifth of that cost (96x78x78, where it does not: 23.7 ms resident, 23.3 tiled).
   if (others && resident_time(fit, plans, ctxs, ncu, K) > 0.8 * cells / TILED_RATE) return 0;
-  {
-    long long items = 0;
-    for (int i = 0; i < n; ++i) items += march64_blocks(ctxs[i]->g);
-    if (!br.make(n, ncu, items, bs)) return 0;       // no room: the tiled launches need less
-    HIPCHK(hipGetLastError());
-    std::vector<double> sweeps_left(n, 1e18);    // estimated
-    std::vector<long long> it_seen(n, 0);
-    std::vector<double> ri_seen(n, 0.0);
-    std::vector<ResidentProb<float>> tab(2 * n);
-    std::vector<BatchProb> hp;
-    std::vector<BatchR64> ref(2 * n);
-    std::vector<int> of(ncu), ref_of;
-    for (;;) {
-      // the problems of the next launches, and their splits
-      std::vector<int> order, set;
-      for (int i = 0; i < n; ++i)
-        if (h_ctl[i].state == CTL_RUN && !plans[i].empty()) order.push_back(i);
-      if (order.empty()) break;
-      std::stable_sort(order.begin(), order.end(),
-                       [&](int a, int b) { return sweeps_left[a] > sweeps_left[b]; });
-      std::vector<const ResidentPlan *> pick;
-      choose_resident(order, plans, ctxs, ncu, set, pick);
-      hp.assign(n, BatchProb{});
-      for (int i = 0; i < n; ++i) hp[i].ctl = d_ctl + i;
-      int blk = 0, lds = 0;
-      ref_of.clear();
-      for (size_t k = 0; k < set.size(); ++k) {
-        const int i = set[k];
-        socfv_ctx *c = ctxs[i];
-        const ResidentPlan &pl = *pick[k];
-        BatchProb &b = hp[i];
-        b.gx = pl.gx; b.gy = pl.gy; b.gz = pl.gz;
-        b.tile0 = blk;
-        b.rpart = c->partial;
-        b.rnblk = march64_blocks(c->g);
-        for (int par = 0; par < 2; ++par) {
-          ResidentProb<float> &e = tab[par * n + k];
-          e = ResidentProb<float>{};
-          e.a = S[i].sweep_args<float>(c->s32[par], c->s32[par ^ 1], true,
-                                       br.part + (long long)NV * blk);
-          e.a.w = faces32(c);
-          e.a.gate = &d_ctl[i].state;
-          e.p = br.args(pl, blk, ncu);
-          e.p.abort = &d_ctl[i].lost;
-          e.p.limit = c->wait_limit;
-          e.p.fill = &d_ctl[i].fill;
-          e.blk0 = blk;
-          e.C = pl.C;
-          // the refresh after this chunk takes the correction that the chunk wrote
-          BatchR64 &q = ref[par * n + k];
-          q = BatchR64{};
-          q.a.g = c->g; q.a.flags = c->flags; q.a.w = faces64(c); q.a.kappa = c->kappa;
-          q.a.delta = c->s32[par ^ 1]; q.a.r0 = c->r0;
-          q.a.s_in = p[i].s_in; q.a.s_eq = p[i].s_eq; q.a.Da = p[i].Da;
-          q.a.pinned = S[i].pinned; q.a.lo = S[i].lo; q.a.hi = S[i].hi;
-          q.a.partial = c->partial;
-          q.a.gate = &d_ctl[i].state;
-          q.a.gate_val = CTL_REFRESH;
-          q.a.sel = &d_ctl[i].cur;
-          q.a.pair[0] = c->s64[0];
-          q.a.pair[1] = c->s64[1];
-          march64_shape(c->g, q.gx, q.gy, q.gz, q.a.zc);
-          q.blk0 = (int)ref_of.size();
-        }
-        ref_of.insert(ref_of.end(), march64_blocks(c->g), (int)k);
-        for (int t = 0; t < pl.blocks(); ++t) of[blk++] = (int)k;
-        lds = std::max(lds, pl.lds);
+  long long items = 0;
+  for (int i = 0; i < n; ++i) items += march64_blocks(ctxs[i]->g);
+  if (!br.make(n, ncu, items, bs)) return 0;       // no room: the tiled launches need less
+  HIPCHK(hipGetLastError());
+  std::vector<double> sweeps_left(n, 1e18);    // estimated
+  std::vector<long long> it_seen(n, 0);
+  std::vector<double> ri_seen(n, 0.0);
+  std::vector<ResidentProb<float>> tab(2 * n);
+  std::vector<BatchProb> hp;
+  std::vector<BatchR64> ref(2 * n);
+  std::vector<int> of(ncu), ref_of;
+  for (;;) {
+    // the problems of the next launches, and their splits
+    std::vector<int> order, set;
+    for (int i = 0; i < n; ++i)
+      if (h_ctl[i].state == CTL_RUN && !plans[i].empty()) order.push_back(i);
+    if (order.empty()) break;
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int a, int b) { return sweeps_left[a] > sweeps_left[b]; });
+    std::vector<const ResidentPlan *> pick;
+    choose_resident(order, plans, ctxs, ncu, set, pick);
+    hp.assign(n, BatchProb{});
+    for (int i = 0; i < n; ++i) hp[i].ctl = d_ctl + i;
+    int blk = 0, lds = 0;
+    ref_of.clear();
+    for (size_t k = 0; k < set.size(); ++k) {
+      const int i = set[k];
+      socfv_ctx *c = ctxs[i];
+      const ResidentPlan &pl = *pick[k];
+      BatchProb &b = hp[i];
+      b.gx = pl.gx; b.gy = pl.gy; b.gz = pl.gz;
+      b.tile0 = blk;
+      b.rpart = c->partial;
+      b.rnblk = march64_blocks(c->g);
+      for (int par = 0; par < 2; ++par) {
+        ResidentProb<float> &e = tab[par * n + k];
+        e = ResidentProb<float>{};
+        e.a = S[i].sweep_args<float>(c->s32[par], c->s32[par ^ 1], true,
+                                     br.part + (long long)NV * blk);
+        e.a.w = faces32(c);
+        e.a.gate = &d_ctl[i].state;
+        e.p = br.args(pl, blk, ncu);
+        e.p.abort = &d_ctl[i].lost;
+        e.p.limit = c->wait_limit;
+        e.p.fill = &d_ctl[i].fill;
+        e.blk0 = blk;
+        e.C = pl.C;
+        // the refresh after this chunk takes the correction that the chunk wrote
+        BatchR64 &q = ref[par * n + k];
+        q = BatchR64{};
+        q.a.g = c->g; q.a.flags = c->flags; q.a.w = faces64(c); q.a.kappa = c->kappa;
+        q.a.delta = c->s32[par ^ 1]; q.a.r0 = c->r0;
+        q.a.s_in = p[i].s_in; q.a.s_eq = p[i].s_eq; q.a.Da = p[i].Da;
+        q.a.pinned = S[i].pinned; q.a.lo = S[i].lo; q.a.hi = S[i].hi;
+        q.a.partial = c->partial;
+        q.a.gate = &d_ctl[i].state;
+        q.a.gate_val = CTL_REFRESH;
+        q.a.sel = &d_ctl[i].cur;
+        q.a.pair[0] = c->s64[0];
+        q.a.pair[1] = c->s64[1];
+        march64_shape(c->g, q.gx, q.gy, q.gz, q.a.zc);
+        q.blk0 = (int)ref_of.size();
       }
-      HIPCHK(hipMemcpyAsync(br.tab, tab.data(), sizeof(ResidentProb<float>) * 2 * n,
-                            hipMemcpyHostToDevice, bs));
-      HIPCHK(hipMemcpyAsync(br.of, of.data(), sizeof(int) * blk, hipMemcpyHostToDevice, bs));
-      HIPCHK(hipMemcpyAsync(br.refresh, ref.data(), sizeof(BatchR64) * 2 * n,
-                            hipMemcpyHostToDevice, bs));
-      HIPCHK(hipMemcpyAsync(br.refresh_of, ref_of.data(), sizeof(int) * ref_of.size(),
-                            hipMemcpyHostToDevice, bs));
-      HIPCHK(hipMemcpyAsync(d_probs, hp.data(), sizeof(BatchProb) * n, hipMemcpyHostToDevice, bs));
-      // chunks until the next read: up to four, not far beyond the first problem's end (its
-      // workgroups would idle)
-      double least = 1e18;
-      for (int i : set) least = std::min(least, sweeps_left[i]);
-      const int rounds = least > 1e17 ? 2 : (int)std::max(1.0, std::min(4.0, std::ceil(least / K)));
-      for (int r = 0; r < rounds; ++r) {
-        const unsigned tag = br.take(K, bs);
-        {
-          const Turn turn(ctxs[0]->dev, ctxs[0]->ncu, blk, bs, ctxs[0]->turn);
-          launch_resident_batch<float>(br.tab + (r & 1) * n, br.of, blk, lds, tag, K, bs);
-        }
-        launch_batch_reduce(d_probs, n, br.part, d_out, bs);
-        launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_CHUNK, d_out, K, bs);
-        launch_batch_refresh(br.refresh + (r & 1) * n, br.refresh_of, (int)ref_of.size(), bs);
-        // the chunk's output is the next one's input
-        for (int i : set) std::swap(ctxs[i]->s32[0], ctxs[i]->s32[1]);
-        launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_REFRESH, nullptr, 0, bs);
-      }
-      HIPCHK(hipGetLastError());
-      HIPCHK(hipMemcpyAsync(h_ctl, d_ctl, sizeof(SolveCtl) * n, hipMemcpyDeviceToHost, bs));
-      HIPCHK(hipStreamSynchronize(bs));
-      for (int i : set) {
-        const SolveCtl &h = h_ctl[i];
-        if (h.state == CTL_DIVERGED)
-          return fail(SOCFV_DIVERGED, "batch problem %d diverged at sweep %lld", i, h.it);
-        if (h.state == CTL_LOST) {
-          // the first chunk that did not run read what the last one that ran wrote
-          const long long ran = (h.it - it_seen[i]) / K;
-          if ((rounds - ran) & 1) std::swap(ctxs[i]->s32[0], ctxs[i]->s32[1]);
-        }
-        if (ri_seen[i] > 0 && h.ri > 0 && h.ri < ri_seen[i] && h.it > it_seen[i])
-          sweeps_left[i] = std::log(p[i].tol / h.ri) * (double)(h.it - it_seen[i]) /
-                           std::log(h.ri / ri_seen[i]);
-        it_seen[i] = h.it;
-        ri_seen[i] = h.ri;
-      }
+      ref_of.insert(ref_of.end(), march64_blocks(c->g), (int)k);
+      for (int t = 0; t < pl.blocks(); ++t) of[blk++] = (int)k;
+      lds = std::max(lds, pl.lds);
     }
-    return 0;
+    HIPCHK(hipMemcpyAsync(br.tab, tab.data(), sizeof(ResidentProb<float>) * 2 * n,
+                          hipMemcpyHostToDevice, bs));
+    HIPCHK(hipMemcpyAsync(br.of, of.data(), sizeof(int) * blk, hipMemcpyHostToDevice, bs));
+    HIPCHK(hipMemcpyAsync(br.refresh, ref.data(), sizeof(BatchR64) * 2 * n,
+                          hipMemcpyHostToDevice, bs));
+    HIPCHK(hipMemcpyAsync(br.refresh_of, ref_of.data(), sizeof(int) * ref_of.size(),
+                          hipMemcpyHostToDevice, bs));
+    HIPCHK(hipMemcpyAsync(d_probs, hp.data(), sizeof(BatchProb) * n, hipMemcpyHostToDevice, bs));
+    // chunks until the next read: up to four, not far beyond the first problem's end (its
+    // workgroups would idle)
+    double least = 1e18;
+    for (int i : set) least = std::min(least, sweeps_left[i]);
+    const int rounds = least > 1e17 ? 2 : (int)std::max(1.0, std::min(4.0, std::ceil(least / K)));
+    for (int r = 0; r < rounds; ++r) {
+      const unsigned tag = br.take(K, bs);
+      {
+        const Turn turn(ctxs[0]->dev, ctxs[0]->ncu, blk, bs, ctxs[0]->turn);
+        launch_resident_batch<float>(br.tab + (r & 1) * n, br.of, blk, lds, tag, K, bs);
+      }
+      launch_batch_reduce(d_probs, n, br.part, d_out, bs);
+      launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_CHUNK, d_out, K, bs);
+      launch_batch_refresh(br.refresh + (r & 1) * n, br.refresh_of, (int)ref_of.size(), bs);
+      // the chunk's output is the next one's input
+      for (int i : set) std::swap(ctxs[i]->s32[0], ctxs[i]->s32[1]);
+      launch_batch_control(d_probs, n, nullptr, 0, nullptr, BATCH_REFRESH, nullptr, 0, bs);
+    }
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(h_ctl, d_ctl, sizeof(SolveCtl) * n, hipMemcpyDeviceToHost, bs));
+    HIPCHK(hipStreamSynchronize(bs));
+    for (int i : set) {
+      const SolveCtl &h = h_ctl[i];
+      if (h.state == CTL_DIVERGED)
+        return fail(SOCFV_DIVERGED, "batch problem %d diverged at sweep %lld", i, h.it);
+      if (h.state == CTL_LOST) {
+        // the first chunk that did not run read what the last one that ran wrote
+        const long long ran = (h.it - it_seen[i]) / K;
+        if ((rounds - ran) & 1) std::swap(ctxs[i]->s32[0], ctxs[i]->s32[1]);
+      }
+      if (ri_seen[i] > 0 && h.ri > 0 && h.ri < ri_seen[i] && h.it > it_seen[i])
+        sweeps_left[i] = std::log(p[i].tol / h.ri) * (double)(h.it - it_seen[i]) /
+                         std::log(h.ri / ri_seen[i]);
+      it_seen[i] = h.it;
+      ri_seen[i] = h.ri;
+    }
   }
+  return 0;
 }
 
 // outputs of state s: per-block partials at `partial` (outputs_blocks x NV2 doubles), the
