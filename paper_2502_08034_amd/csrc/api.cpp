@@ -2595,18 +2595,22 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     double total_prev = 0.0, du = INFINITY, un = 0.0;
     int m = p->cg_max;
     int guess = 16, from = -1;           // CG iterations to enqueue; where a stalled CG goes on
+    int calm = 0;                        // reads in a row after which no step had stalled
     double seen = 0.0;
     unsigned tag = 1;                    // of the whole CG's words
     int status = SOCFV_NOT_CONVERGED;
     while (steps < p->max_steps) {
       const long k = std::min<long>(p->check_every, p->max_steps - steps);
-      // A step is enqueued with as many CG iterations as the last one took and some more (a launch
-      // past a CG's end returns at once but costs about 2 us); one that needs more is resumed after
-      // the read behind it.  Up to four steps between reads were slower, the iterations being
-      // guessed from older steps: 200 steps on 66x45x45 38.3 ms against 35.9, on 96x64x64 76.7
-      // against 73.7, on 256x128x128 370 against 364.  Steps of one launch need no guess.
+      // A step is enqueued with as many CG iterations as the last ones took and some more (a launch
+      // past a CG's end returns at once but costs about 2 us); one that needs more stalls what
+      // follows, and the read resumes it.  While the flow develops the counts vary and a step at a
+      // time is best; once 16 reads in a row have found none stalled, four steps share a read.  One /
+      // four after 16 / four at once: 200 steps on 66x45x45 32.5 / 34.3 / 44.9 ms, on 96x64x64
+      // 73.4 / 73.1 / 79.5, on 256x128x128 368 / 369 / 375; whole runs at C_CFL 1/2 on 66x45x45
+      // 1.72 / 1.53 / 1.66 s, on 96x48x48 2.45 / 2.21 / 2.36.  (Eight steps a read after 8: 36.2,
+      // 74.3, 370 ms; 1.56, 2.28 s.)  Steps of one launch need no guess.
       for (long s = 0; s < k;) {
-        const long grp = whole ? std::min<long>(k - s, 64) : 1;
+        const long grp = std::min<long>(k - s, whole ? 64 : calm >= 16 ? 4 : 1);
         for (long q = 0; whole && q < grp; ++q) {
           if (tag > 0xffffffffu - (2u * m + 2u)) {
             launch_fill_f64((double *)a.words, CGW_WORDS, 0.0, c->st);
@@ -2621,12 +2625,12 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
           launch_flow_project(a, m, c->st);
           tag += 2u * m + 2u;
         }
-        if (!whole) {
-          if (from < 0) {
+        for (long q = 0; !whole && q < grp; ++q) {
+          if (q > 0 || from < 0) {
             launch_flow_predict(a, c->st);
             launch_flow_cg_init(a, c->st);
           }
-          const int j0 = std::max(from, 0);
+          const int j0 = q == 0 ? std::max(from, 0) : 0;
           for (int j = j0; j < std::min(m, j0 + guess); ++j) launch_flow_cg_iter(a, j, m, c->st);
           launch_flow_project(a, m, c->st);
         }
@@ -2650,10 +2654,12 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
         } else if (c->hres[FS_STALL] != 0.0) {
           from = (int)c->hres[FS_CG_STEP];
           guess = std::max(8, from / 2);
+          calm = -1;
           launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
         } else if (!whole) {
           from = -1;
-          guess = (int)std::ceil(1.2 * (c->hres[FS_CG_TOTAL] - seen)) + 3;
+          ++calm;
+          guess = (int)std::ceil(1.2 * (c->hres[FS_CG_TOTAL] - seen) / (double)ran) + 3;
         }
         seen = c->hres[FS_CG_TOTAL];
       }

@@ -278,3 +278,20 @@ def test_the_largest_boxes_of_the_single_launch(sv):
         assert runs[0][4].cg_iterations == runs[1][4].cg_iterations
         for x, y in zip(*(r[:4] for r in runs)):
             assert torch.equal(x, y), shape
+
+
+def test_steps_that_share_a_read_take_the_same_iterations(sv):
+    # far into a run several steps are enqueued between reads of the device, at the start one: 300
+    # steps in one call (above the single launch's boxes) are the 300 steps of three calls, each of
+    # which begins with single ones (every CG runs to its cap of 8, also at a call's first step, whose
+    # target comes from no earlier one)
+    g = I.fibres_nonoverlap(110, 32, 32, 2.5, 0.88, 17)
+    ctx = sv.setup_geometry(torch.as_tensor(g.solid, device="cuda"))
+    kw = dict(cfl=3.0, tol=0.0, cg_max=8, cg_theta=1e-30, check_every=100, want_pressure=True)
+    full = sv.solve_stokes(ctx, max_steps=300, **kw)
+    part = sv.solve_stokes(ctx, max_steps=100, **kw)
+    for _ in range(2):
+        part = sv.solve_stokes(ctx, start=part[:4], max_steps=100, **kw)
+    for a, b in zip(full[:4], part[:4]):
+        assert torch.equal(a, b)
+    assert full[4].cg_iterations == 300 * 8
