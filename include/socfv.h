@@ -357,13 +357,15 @@ int socfv_set_tiles(socfv_ctx *c, int tile_y, int z_chunk, int z_chunk2, int two
 int socfv_autotune(socfv_ctx *c, int sweeps, int best[3], void *hip_stream);
 
 /*
- * Longest time (s, default 1, at most 3600) that a workgroup of a launch whose workgroups wait for
+ * Longest time (s, default 0.005, at most 3600) that a workgroup of a launch whose workgroups wait for
  * each other does wait: chunks of sweeps or Nernst iterations in one launch, batched ones, and the
  * flow step's single-launch CG.  They run together on an otherwise idle GPU; where other work holds
- * CUs for longer, the launch is given up, its input is intact, and the call goes on with the other
- * launches: single solves in that precision (or Nernst iterations) from then on for this context, a
- * batch and a flow step for the rest of the call.  A given-up launch shows in no result and in no
- * statistic but the time.  0 gives up at the first value that is not there yet.
+ * CUs for longer (another process's launches, say), the launch is given up, its input is intact, and
+ * the call goes on with the other launches; this one's kind is tried again after 2 chunks of sweeps
+ * (flow steps), after a further loss 4, and so on up to 1,024, in later calls on the context too (a
+ * batch tries a problem three times more, then sweeps it in the tiled launches).  FP32 sweeps, flow
+ * steps and their counts are the same either way, FP64 sweeps to their rounding.  A given-up launch
+ * shows in no statistic but the time.  0 gives up at the first value that is not there yet.
  */
 int socfv_set_wait_limit(socfv_ctx *c, double seconds);
 

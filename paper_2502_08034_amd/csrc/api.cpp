@@ -60,7 +60,7 @@ double now_s() {
 // of the compute units and wait for the time limit; so those in flight on a device hold at most
 // its compute units, one a workgroup, and a launch beyond that is ordered behind the oldest ones
 // by their events.  Small ones still run side by side.  Work of other streams that does end by
-// itself needs no turn, and another process's is left to the time limit.
+// itself needs no turn, and another process's is left to the time limit (Tries).
 class Turn {
  public:
   Turn(int dev, int ncu, long long blocks, hipStream_t st, hipEvent_t ev)
@@ -118,6 +118,24 @@ class Turn {
   hipEvent_t ev_;
 };
 
+// Tries of launches whose workgroups wait for each other: after one that was given up, the next
+// chunks (or steps) take the other launches, two of them after the first loss, twice as many after
+// each further one (at most 1,024) and half as many again after each that ran.  With the limit of
+// 5 ms several processes on one GPU, whose launches can each hold a part of its compute units, make
+// headway: four of them (problems made and solved in FP32, FP64 and the flow step) 4 rounds a second
+// together at 1 s and no second try, 46 at 5 ms, 53 at 1 ms, 33 at 20 ms, and 31 without resident
+// launches; two of them 38, 50, 49, 49 and 19.
+struct Tries {
+  int losses = 0;
+  long skip = 0;
+  bool take() { return skip == 0 || (--skip, false); }
+  void lost() {
+    losses = std::min(losses + 1, 10);
+    skip = 1l << losses;
+  }
+  void ran() { losses = std::max(losses - 1, 0); }
+};
+
 }  // namespace
 
 struct socfv_ctx {
@@ -157,13 +175,14 @@ struct socfv_ctx {
   // next tag
   ResidentPlan res{}, res64{}, resn{};   // (resn: the Nernst iteration's)
   bool res_planned = false;
+  Tries try32, try64, tryn;
   std::vector<ResidentPlan> batch_plans[2];   // resident_plans in FP32, FP64 (made at first use:
   bool batch_planned[2] = {false, false};     // up to 0.1 ms)
   unsigned long long *inbox = nullptr;
   void *res_diag = nullptr;
   long long inbox_words = 0;
   unsigned tag = 1;
-  unsigned long long wait_limit = 100000000ull;   // ticks of the 100 MHz clock: 1 s
+  unsigned long long wait_limit = 500000ull;   // ticks of the 100 MHz clock: 5 ms
   int ncu = 1;                   // compute units of the device (for the tile choice)
   int dev = 0;                   // device holding the context's buffers
   // last forward solution
@@ -512,8 +531,14 @@ struct Solver {
     return sizeof(T) == 4 ? c->res : c->res64;
   }
   template <typename T>
-  bool resident(long k) const {          // a chunk of k sweeps
-    return k >= RESIDENT_LEAST && res_plan<T>().C > 0 && c->inbox && !c->tiles_fixed;
+  Tries &tries() const {
+    return sizeof(T) == 4 ? c->try32 : c->try64;
+  }
+  // does the next chunk, of k sweeps, go into a resident launch? (asked once a chunk)
+  template <typename T>
+  bool resident(long k) const {
+    return k >= RESIDENT_LEAST && res_plan<T>().C > 0 && c->inbox && !c->tiles_fixed &&
+           tries<T>().take();
   }
 
   // Enqueue k sweeps a.s -> a.s_new as one resident launch (fill: device flag, nullable);
@@ -544,20 +569,22 @@ struct Solver {
     return rp.blocks();
   }
 
-  // The same with the partials reduced on the host; false if the launch was given up (its input
-  // is as it was, and this context takes the other launches from then on).
+  // The same with the partials reduced on the host; ran is false if the launch was given up (its
+  // input is as it was).
   template <typename T>
   int resident_chunk(const SweepArgs<T> &a, int k, bool adj, double out[NV], bool &ran) {
-    return resident_sums(launch_resident_sweeps<T>(a, k, adj, nullptr), res_plan<T>(), out, ran);
+    return resident_sums(launch_resident_sweeps<T>(a, k, adj, nullptr), tries<T>(), out, ran);
   }
-  int resident_sums(long long nb, ResidentPlan &plan, double out[NV], bool &ran) {
+  int resident_sums(long long nb, Tries &t, double out[NV], bool &ran) {
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(&c->hctl->lost, &c->dctl->lost, sizeof(int), hipMemcpyDeviceToHost,
                           c->st));
     TRY(reduce_to_host(c, (int)nb, NV, 0u, out));
     ran = !c->hctl->lost;
-    if (!ran) {
-      plan.C = 0;
+    if (ran) {
+      t.ran();
+    } else {
+      t.lost();
       launch_fill_f32((float *)&c->dctl->lost, 1, 0.0f, c->st);
       HIPCHK(hipGetLastError());
     }
@@ -690,12 +717,14 @@ struct Solver {
     for (;;) {
       int ks[G], from[G];
       int nch = 0;
+      bool tried = false;                // a resident launch among them
       long long enq = known;
       for (; nch < ng && enq < budget; ++nch) {
         const int k = (int)std::min<long long>(K, budget - enq);
         from[nch] = cd;
         long long nb;
         if (resident<float>(k)) {
+          tried = true;
           HIPCHK(hipEventRecord(c->evp[4 * nch], c->st));
           SweepArgs<float> a = sweep_args<float>(c->s32[cd], c->s32[cd ^ 1], true, c->partial);
           a.w = faces32(c);
@@ -743,18 +772,19 @@ struct Solver {
       for (int g = nch - 1; g >= 0 && g >= nch - (h.cycles - cyc0); --g) msref += refresh_ms[g];
       if (h.state == CTL_LOST) {
         // the chunk after the last one that ran was given up: its input is as it was, and the
-        // two-sweep launches go on from there
+        // next group goes on from there
         long long it = known;
         int g = 0;
         while (it < h.it) it += ks[g++];
         cd = from[g];
-        c->res.C = 0;
+        c->try32.lost();
         h.state = CTL_RUN;
         h.lost = 0;
         known = h.it;
         HIPCHK(hipMemcpyAsync(c->dctl, c->hctl, sizeof(SolveCtl), hipMemcpyHostToDevice, c->st));
         continue;
       }
+      if (tried) c->try32.ran();
       known = h.it;
       if (h.state == CTL_DIVERGED || h.state == CTL_DONE || h.state == CTL_STOP || nch == 0) break;
       // next group: about half the chunks the residual's decay rate since the last read
@@ -972,6 +1002,9 @@ double resident_time(std::vector<int> order, const std::vector<std::vector<Resid
   return total;
 }
 
+// Given-up launches of a problem after which a batch sweeps it in tiled launches.
+constexpr int BATCH_LOSSES = 3;
+
 // Cells per us that the tiled launches sweep: boxes of 4 to 8 million cells, alone and with smaller
 // ones, 212 to 232 thousand.
 constexpr double TILED_RATE = 220e3;
@@ -1012,6 +1045,7 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
   HIPCHK(hipGetLastError());
   std::vector<double> sweeps_left(n, 1e18);    // estimated
   std::vector<long long> it_seen(n, 0);
+  std::vector<int> losses(n, 0);
   std::vector<double> ri_seen(n, 0.0);
   std::vector<ResidentProb<float>> tab(2 * n);
   std::vector<BatchProb> hp;
@@ -1110,6 +1144,11 @@ int batch_resident(int n, socfv_ctx *const *ctxs, const socfv_params *p, Solver 
         // the first chunk that did not run read what the last one that ran wrote
         const long long ran = (h.it - it_seen[i]) / K;
         if ((rounds - ran) & 1) std::swap(ctxs[i]->s32[0], ctxs[i]->s32[1]);
+        if (++losses[i] <= BATCH_LOSSES) {           // tried again
+          h_ctl[i].state = CTL_RUN;
+          h_ctl[i].lost = 0;
+          HIPCHK(hipMemcpyAsync(d_ctl + i, h_ctl + i, sizeof(SolveCtl), hipMemcpyHostToDevice, bs));
+        }
       }
       if (ri_seen[i] > 0 && h.ri > 0 && h.ri < ri_seen[i] && h.it > it_seen[i])
         sweeps_left[i] = std::log(p[i].tol / h.ri) * (double)(h.it - it_seen[i]) /
@@ -1626,7 +1665,7 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
     while (S.it < p->max_iter) {
       const long k = std::min<long>(K, p->max_iter - S.it);
       bool ran = false;
-      if (whole && c->resn.C && k >= RESIDENT_LEAST_NERNST) {
+      if (whole && k >= RESIDENT_LEAST_NERNST && c->tryn.take()) {
         SweepArgs<double> w = S.sweep_args<double>(c->s64[cur], c->s64[cur ^ 1], false, c->partial);
         w.w = faces64(c);
         double *half[2] = {eta, eta + n};
@@ -1638,7 +1677,7 @@ int socfv_solve_nernst(socfv_ctx *c, const socfv_params *p, double omega, double
           const Turn turn(c->dev, c->ncu, c->resn.blocks(), c->st, c->turn);
           launch_resident_nernst(w, c->resn, r, c->st);
         }
-        TRY(S.resident_sums(c->resn.blocks(), c->resn, out, ran));
+        TRY(S.resident_sums(c->resn.blocks(), c->tryn, out, ran));
         if (ran) {
           a.eta = r.eta_new;
           cur ^= 1;
@@ -2570,16 +2609,17 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     a.pdiv = a.pdu + 6ll * a.nbf;
     a.pfl = a.pdiv + 4ll * a.nbc;
     a.sc = a.pfl + a.nbc;
-    bool whole = flow_cg_whole(a, c->ncu) && p->cg_max < (1 << 20);
-    if (whole) {
+    const bool single = flow_cg_whole(a, c->ncu) && p->cg_max < (1 << 20);
+    int *lost = nullptr;
+    if (single) {
       void *w = nullptr;
       TRY(alloc(&w, sizeof(unsigned long long) * (size_t)(CGW_WORDS + 1)));
       a.words = (unsigned long long *)w;
-      a.lost = (int *)(a.words + CGW_WORDS);
+      lost = (int *)(a.words + CGW_WORDS);
       a.limit = c->wait_limit;
     }
     TRY(enter(c, hip_stream));
-    if (whole) launch_fill_f64((double *)a.words, CGW_WORDS + 1, 0.0, c->st);
+    if (single) launch_fill_f64((double *)a.words, CGW_WORDS + 1, 0.0, c->st);
     // start from rest with zero pressure, or resume from the caller's velocity and pressure;
     // zero partials make the first step's CG run to its cap
     if (!p->resume)
@@ -2598,6 +2638,7 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
     int calm = 0;                        // reads in a row after which no step had stalled
     double seen = 0.0;
     unsigned tag = 1;                    // of the whole CG's words
+    Tries tries;
     int status = SOCFV_NOT_CONVERGED;
     while (steps < p->max_steps) {
       const long k = std::min<long>(p->check_every, p->max_steps - steps);
@@ -2610,6 +2651,8 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
       // 1.72 / 1.53 / 1.66 s, on 96x48x48 2.45 / 2.21 / 2.36.  (Eight steps a read after 8: 36.2,
       // 74.3, 370 ms; 1.56, 2.28 s.)  Steps of one launch need no guess.
       for (long s = 0; s < k;) {
+        const bool whole = single && from < 0 && tries.take();
+        a.lost = whole ? lost : nullptr;
         const long grp = std::min<long>(k - s, whole ? 64 : calm >= 16 ? 4 : 1);
         for (long q = 0; whole && q < grp; ++q) {
           if (tag > 0xffffffffu - (2u * m + 2u)) {
@@ -2648,15 +2691,17 @@ int socfv_solve_stokes(socfv_ctx *c, const socfv_flow_params *p, double *ux, dou
         if (c->hres[FS_STALL] == 2.0) {
           // given up: the step again, in separate launches, from the pressure before it
           if ((grp - ran) & 1) std::swap(a.p, a.q);
-          whole = false;
-          a.lost = nullptr;
+          tries.lost();
+          launch_fill_f64((double *)lost, 1, 0.0, c->st);
           launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
         } else if (c->hres[FS_STALL] != 0.0) {
           from = (int)c->hres[FS_CG_STEP];
           guess = std::max(8, from / 2);
           calm = -1;
           launch_fill_f64(a.sc + FS_STALL, 1, 0.0, c->st);
-        } else if (!whole) {
+        } else if (whole) {
+          tries.ran();
+        } else {
           from = -1;
           ++calm;
           guess = (int)std::ceil(1.2 * (c->hres[FS_CG_TOTAL] - seen) / (double)ran) + 3;

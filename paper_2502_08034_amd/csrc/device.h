@@ -234,4 +234,18 @@ __device__ __forceinline__ bool get_value(const unsigned long long *p, unsigned 
   }
 }
 
+// Time that a wait has taken, in ticks of the 100 MHz clock, for its limit.  A step between two
+// looks counts for at most 1 ms: one in which this process's work was off the chip is longer.
+// (32 bits each: the kernels that wait have few registers left.)
+struct Waited {
+  unsigned last = 0;
+  float sum = -1.f;             // below 0: not looked yet
+  __device__ __forceinline__ bool over(float limit) {
+    const unsigned now = (unsigned)wall_clock64();
+    sum = sum < 0.f ? 0.f : sum + (float)min(now - last, 100000u);
+    last = now;
+    return sum >= limit;
+  }
+};
+
 }  // namespace socfv

@@ -537,12 +537,10 @@ k_flow_cg_whole(FlowArgs a, int m, unsigned tag0) {
   const unsigned turns = a.limit < 10000 ? 0u : 255u;
   auto wait = [&](int &dead, auto &&all) {
     unsigned spins = 0;
-    unsigned long long t0 = 0;
+    Waited waited;
     while (!all()) {
       if ((++spins & turns) == 0) {
-        const unsigned long long now = wall_clock64();
-        if (t0 == 0) t0 = now;
-        if (now - t0 >= a.limit ||
+        if (waited.over((float)a.limit) ||
             __hip_atomic_load(a.lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
           dead = 1;
           __hip_atomic_store(a.lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

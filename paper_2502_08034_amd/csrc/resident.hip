@@ -18,10 +18,10 @@
 // sweep arrived, that is after the neighbour has read the slot.
 //
 // Waits.  All blocks must be resident together: the grid is at most one block per CU and every
-// CU holds one.  Should blocks wait for CUs that other work holds, or never get them, every wait
-// ends by a time limit: the block raises the abort flag, every block leaves, no state is lost
-// (the launch writes only its output buffer), and the host goes on with launches of the
-// two-sweep kernel.
+// CU holds one.  Should blocks wait for CUs that other work holds, or never get them (two
+// processes' launches can each hold a part of them), every wait ends by a time limit: the block
+// raises the abort flag, every block leaves, no state is lost (the launch writes only its output
+// buffer), and the host goes on with the other launches for a while.
 #include "device.h"
 
 #include <algorithm>
@@ -456,7 +456,7 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
     // the neighbours' values: every load of a round in flight at once
     const unsigned long long *const mine = slot + b * p.block_words + t * WN;
     unsigned spins = 0;
-    unsigned long long t0 = 0;
+    Waited waited;
     bool gone = false, ok;
     do {
       ok = true;
@@ -466,9 +466,7 @@ __device__ __forceinline__ void resident_block(const SweepArgs<T> &a, const Resi
       ok &= get_value<T>(mine + NJ * RT * WN, tag, va) | !below;
       ok &= get_value<T>(mine + (NJ + 1) * RT * WN, tag, vb) | !above;
       if (!ok && (p.limit == 0 || (++spins & 255u) == 0)) {
-        const unsigned long long now = wall_clock64();
-        if (t0 == 0) t0 = now;
-        gone = now - t0 >= p.limit ||
+        gone = waited.over((float)p.limit) ||
                __hip_atomic_load(p.abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
       }
     } while (!ok && !gone);

@@ -293,3 +293,49 @@ def test_autotune_leaves_the_results(sv, shape):
     t, tt = sv.solve_soc_steady(pb.ctx, p)
     assert tt.iterations == st.iterations == 80 and (tt.tile_y, tt.z_chunk) == (ty, zc)
     assert torch.equal(s, t)
+
+
+WORKER = """
+import sys, time
+sys.path.insert(0, sys.argv[1])
+import torch
+from paper_2502_08034_amd import inputs as I, socfv as sv
+boxes = [(64, 32, 32), (175, 89, 89), (128, 64, 64), (96, 48, 48)]
+kw = dict(tol=0.0, max_iter=1000, check_every=200, s_in=1.0, s_eq=0.0, Da=0.45, mode=0)
+worst, sums = 0.0, {}
+for k in range(-4, 40):
+    solid, u = I.plug_flow_case(*boxes[(k + int(sys.argv[2])) % 4], 0.7)
+    pb = sv.Problem.create(solid, *u)
+    t = time.perf_counter()
+    s, st = sv.solve_soc_steady(pb.ctx, sv.params(precision="fp32", **kw))
+    r, _ = sv.solve_soc_steady(pb.ctx, sv.params(precision="fp64", **kw))
+    ux = sv.solve_stokes(pb.ctx, cfl=3.0, max_steps=20, tol=0.0)[0]
+    torch.cuda.synchronize()
+    if k >= 0:                                   # (the first ones load the kernels)
+        worst = max(worst, time.perf_counter() - t)
+    got = [float(v.double().sum()) for v in (s, r, ux)]
+    want = sums.setdefault(solid.shape, got)
+    assert st.iterations == 1000
+    assert got[0] == want[0] and abs(got[1] - want[1]) <= 1e-12 * abs(want[1]) and got[2] == want[2]
+print(worst)
+"""
+
+
+def test_processes_that_share_the_gpu_make_headway(sv):
+    # launches of several processes can each hold a part of the CUs and wait for the rest: they give
+    # up soon, do some chunks otherwise and try again.  Without contention the three calls take 0.02
+    # to 0.07 s; a launch that waits a second, or a context that then stays with the slow launches,
+    # would show.  The results are the same
+    import subprocess
+    import sys
+    import os
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    procs = [subprocess.Popen([sys.executable, "-c", WORKER, root, str(k)], stdout=subprocess.PIPE,
+                              text=True) for k in range(3)]
+    try:
+        out = [p.communicate(timeout=100)[0] for p in procs]
+    finally:
+        for p in procs:
+            p.kill()
+    assert all(p.returncode == 0 for p in procs)
+    assert all(float(o) < 0.7 for o in out), out
