@@ -983,7 +983,8 @@ std::vector<ResidentPlan> batch_plans(socfv_ctx *c, int bytes) {
 
 // Modelled time per sweep of resident launches over the problems of `order`, in chunks of K sweeps
 // (their launches, the read of the states and the refreshes: 40 us a chunk on 64x32x32, 90 on
-// 160x96x96).
+// 160x96x96 alone, 120 taken: 160x96x96 and 128x64x64 beside 300x160x128 in chunks of 20, 200
+// sweeps, 9.0 to 9.6 ms resident, 8.5 tiled).
 double resident_time(std::vector<int> order, const std::vector<std::vector<ResidentPlan>> &plans,
                      socfv_ctx *const *ctxs, int ncu, int K) {
   double total = 0;
@@ -996,7 +997,7 @@ double resident_time(std::vector<int> order, const std::vector<std::vector<Resid
       us = std::max(us, q->us - q->words_us);
       words += q->words_us;
     }
-    total += us + words + 90.0 / K;
+    total += us + words + 120.0 / K;
     for (int i : set) order.erase(std::find(order.begin(), order.end(), i));
   }
   return total;
